@@ -263,7 +263,11 @@ fdkv_status fdkv_decode_workspace(const fdkv_dims* dims, int32_t batch, int32_t 
  *   q            device [batch][Hq][d]
  *   out          device [batch][Hq][d]
  *   sm_scale     logit scale (the paper uses 1/sqrt(d))
- *   ws           device workspace of >= fdkv_decode_workspace() bytes
+ *   ws           device workspace of >= fdkv_decode_workspace() bytes; with four
+ *                times that (two times at Hq / Hkv = 8) a call of few chunks of
+ *                512 tokens (at most 192 over all sequences and KV heads, bf16
+ *                or FP8 cache) runs its chunks on several workgroups each, with
+ *                the same results in about half the time
  */
 fdkv_status fdkv_decode_attn(const fdkv_dims* dims, int32_t batch, const int32_t* seq_lens,
                              int32_t max_seq_len, const uint8_t* modes, const uint64_t* seg_offsets,
@@ -371,7 +375,8 @@ fdkv_status fdkv_decode_spans_workspace(const fdkv_dims* dims, int32_t batch, in
  * and the tail's rows, as fdkv_decode_attn computes it for one span.  A
  * sequence with no token in any part gets o = 0.  spans is a host array of
  * n_spans descriptors; the same limits as fdkv_decode_attn apply to each
- * span, and cap * d * elem_bytes < 2^31 to the tail.
+ * span, and cap * d * elem_bytes < 2^31 to the tail.  The workspace's note at
+ * fdkv_decode_attn applies, but for the last bits of the results.
  */
 fdkv_status fdkv_decode_spans(const fdkv_dims* dims, int32_t batch, int32_t n_spans, const fdkv_span* spans,
                               const fdkv_tail* tail, int32_t layer, const void* q, void* out, float sm_scale,

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void decode_splitk_kernel(DecodeParams P) {
   const int sh = blockIdx.x / P.n_chunks_total;  // seq * hkv + head
   const int head = sh % P.hkv, seq = sh / P.hkv;
   const int part = decode_part(P, slot);
-  const int wgc = slot - P.part[part].base;
+  const int wgc = slot - P.part_base[part];
   const bool tail = part == P.tail_part;
   const int T = P.part[part].lens[seq];
   const int wg_tok0 = wgc * kDecodeWgTokens;

@@ -665,19 +665,29 @@ fdkv_status decode_impl(const fdkv_dims* dims, int32_t batch, int32_t n_spans, c
   int total = 0;
   for (int i = 0; i < n_parts; ++i) {
     const bool t = i == n_spans;
-    p.part[i].base = total;
-    p.part[i].chunks = (int)decode_chunks(t ? tail->cap : spans[i].max_seq_len);
+    p.part_base[i] = total;
     p.part[i].lens = t ? tail->lens : spans[i].seq_lens;
     if (!t) {
       p.part[i].cache = static_cast<const uint8_t*>(spans[i].cache);
       p.part[i].modes = spans[i].modes;
       p.part[i].seg_off = spans[i].seg_offsets;
     }
-    total += p.part[i].chunks;
+    total += (int)decode_chunks(t ? tail->cap : spans[i].max_seq_len);
   }
+  for (int i = n_parts; i < kMaxParts; ++i) p.part_base[i] = INT32_MAX;
+  p.by_chunks.set((uint32_t)std::max(total, 1));
+  p.by_hkv.set((uint32_t)p.hkv);
   p.n_parts = n_parts;
   p.n_chunks_total = total;
   p.tail_part = tail ? n_spans : -1;
+  // A small call (decode_stream.h) spreads its chunks where it merges the
+  // records itself and the workspace holds one per group; otherwise a one-part
+  // call keeps a chunk's groups in one workgroup, which gives the same bits, so
+  // that the two-phase calls and every workspace size agree with the one call.
+  const bool small = p.bf16 && (int64_t)batch * dims->n_kv_heads * total <= kDecodeSmallChunks;
+  const int groups = decode_groups(p.hq / p.hkv);
+  p.n_sub = small && phases == (kPhaseSplit | kPhaseMerge) && ws_bytes / groups >= need ? groups : 1;
+  p.wide = small && p.n_sub == 1 && n_parts == 1 && !tail;
   if (tail) {
     p.tail_k = tail->k;
     p.tail_v = tail->v;
@@ -733,6 +743,7 @@ fdkv_status fdkv_decode_combine(const fdkv_dims* dims, int32_t batch, int32_t n_
   p.batch = batch;
   p.bf16 = dims->dtype != FDKV_F32;
   p.n_chunks_total = n_chunks;
+  p.n_sub = 1;
   const hipError_t e = launch_decode_merge(p, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "decode_merge");
   return FDKV_OK;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "divu.h"
 #include "fdkv_common.h"
 
 namespace fdkv {
@@ -79,6 +80,22 @@ __host__ __device__ __forceinline__ int unit_ppm(int res_ppm, int n_rates, const
 constexpr int kDecodeChunk = 128;
 constexpr int kDecodeWaves = 4;
 constexpr int kDecodeWgTokens = kDecodeChunk * kDecodeWaves;
+// Groups of four waves that share a chunk of a small call (decode_stream.h):
+// 128 tokens a group, or 256 with eight query heads, where the accumulators of
+// sixteen waves would pass the LDS of a workgroup.
+__host__ __device__ constexpr int decode_groups(int G) { return G == 8 ? 2 : 4; }
+// A bf16 or FP8 decode call of at most this many chunks over all (sequence, KV
+// head) pairs is small: its chunks are split over groups of waves.  One
+// workgroup per chunk then leaves at least a quarter of the 256 CUs idle, and
+// each of the others is bound by what one CU can keep in flight (a chunk of
+// 512 tokens is 262 KB).  Per layer on the 8B shape (8 KV heads, one sequence),
+// one workgroup per chunk against groups: 16 chunks 16.0 and 9.4 us, 64 chunks
+// 16.2 and 11.0, 128 chunks 17.8 and 14.0, 200 chunks 18.1 and 17.8, 256 chunks
+// 19.5 and 20.4, 512 chunks 29.1 and 32.6 (more groups than the CUs run at once,
+// and four times the records to merge).  Eight query heads: 128 chunks 24.1 and
+// 18.8 us, 256 chunks 24.6 and 25.9; head dimension 64: 128 chunks 11.5 and
+// 10.2, 256 chunks 12.8 and 14.1.
+constexpr int kDecodeSmallChunks = 192;
 constexpr int kMaxParts = 16;       // compressed spans plus the exact tail of one decode call
 
 // One part of a decode call (a compressed span or the exact tail); its
@@ -88,39 +105,45 @@ struct DecodePart {
   const uint8_t* cache;
   const uint8_t* modes;        // [batch][blocks][hkv], 4-byte aligned
   const uint64_t* seg_off;     // [batch][blocks][hkv]
-  int base, chunks;            // record slots [base, base + chunks) of each (sequence, KV head)
 };
 
+// The first 128 bytes are what a one-part call's split-K workgroup reads: it
+// fetches them in one go.
 struct DecodeParams {
+  DivU by_chunks, by_hkv;      // division by n_chunks_total and hkv
+  int n_chunks_total, hkv, n_blocks, block;  // block: the layer's block
   const void* q;               // [batch][hq][d]
+  float* ws;                   // records [batch][hkv][n_chunks_total][n_sub][G][d + 4]
+  int hq, pos, bsize, topk;    // pos: the layer's position in its block, bsize: layers of the block
+  float wres[3];               // weight of a residual entry of frequency j = 1..3 at this layer
+                               // (B = 2: +-1 for the stored half difference)
+  float scale_log2;            // sm_scale * log2(e)
   bool tokres;                 // residual heads hold a token-level residual set
-  int res_ppm;
+  bool bf16;
+  bool coef8;                  // shared planes and residual values of shared / residual heads in FP8 E4M3
+  bool wide;                   // a chunk's groups of waves in one workgroup (decode_stream.h, kWide)
   int n_rates;                 // routed fractions of the sets (0: every set keeps res_ppm)
-  int rates_ppm[kMaxRates];
-  void* out;                   // [batch][hq][d]
-  float* ws;                   // records [batch][hkv][n_chunks_total][G][d + 4]
-  int block, pos, bsize;       // the layer's block, its position in it, the block size
-  int n_blocks, hkv, hq, d, topk, batch;
+  int res_ppm, tail_part;
   // Parts of one call: compressed spans, then (if tail_part >= 0) the exact
   // tail.  The records of one (sequence, KV head) sit in n_chunks_total
   // slots.  One split-K launch covers every part: workgroup x is slot
   // x % n_chunks_total of (sequence, KV head) x / n_chunks_total.
-  int n_parts, n_chunks_total, tail_part;
   DecodePart part[kMaxParts];
-  float wres[3];               // weight of a residual entry of frequency j = 1..3 at this layer
-                               // (B = 2: +-1 for the stored half difference)
-  float scale_log2;            // sm_scale * log2(e)
-  bool bf16;
-  bool coef8;                  // shared planes and residual values of shared / residual heads in FP8 E4M3
+  int part_base[kMaxParts];    // first record slot of each part; INT32_MAX past the last
   const void* tail_k;          // [batch][hkv][tail_cap][d] of the decoded layer
   const void* tail_v;
-  int tail_cap;
+  int tail_cap, n_parts;
+  int rates_ppm[kMaxRates];
+  void* out;                   // [batch][hq][d]
+  int d, batch;
+  int n_sub;                   // records per chunk: decode_groups(G) (kSpread), else 1
 };
 
 // Part of a decode workgroup's record slot r (parts in slot order; uniform).
 __device__ __forceinline__ int decode_part(const DecodeParams& P, int r) {
   int part = 0;
-  while (part + 1 < P.n_parts && r >= P.part[part + 1].base) ++part;
+#pragma unroll
+  for (int i = 1; i < kMaxParts; ++i) part += r >= P.part_base[i] ? 1 : 0;
   return part;
 }
 
