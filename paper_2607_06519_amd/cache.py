@@ -68,9 +68,8 @@ class CompressedCache:
 
     def decode(self, layer: int, q, out=None, sm_scale: Optional[float] = None, stream=None):
         """One decode step of ``layer`` for queries ``q [batch][Hq][d]``; returns ``out``."""
-        torch = _torch()
         if out is None:
-            out = torch.empty_like(q)
+            out = _torch().empty_like(q)
         scale = 1.0 / math.sqrt(self.dims.head_dim) if sm_scale is None else sm_scale
         B.decode_attn(self.dims, self.batch, self.seq_lens, self.max_seq_len, self.modes, self.offsets,
                       self.buf, layer, q, out, scale, self.ws, stream)
@@ -150,9 +149,8 @@ class Generation:
                  stream)
 
     def decode(self, layer: int, q, out=None, sm_scale: Optional[float] = None, stream=None):
-        torch = _torch()
         if out is None:
-            out = torch.empty_like(q)
+            out = _torch().empty_like(q)
         scale = 1.0 / math.sqrt(self.dims.head_dim) if sm_scale is None else sm_scale
         tail = B.Tail(int(self.lens.data_ptr()), self.cap, int(self.tail_k[layer].data_ptr()),
                       int(self.tail_v[layer].data_ptr()))
