@@ -8,21 +8,29 @@
 // channel s LPR S + j S + c (H = 1: lane j holds channels CPL j ..
 // CPL j + CPL - 1; H = 2: a lane holds one run in each half of the row, so
 // that loads of a segment over the row's lanes are contiguous).  Keys are
-// the bit patterns of the non-negative
-// fp32 magnitudes, which order like the values.  Every lane of a row keeps
-// the same bounds lo < hi with clo = #(keys >= lo) >= k and chi = #(keys >=
-// hi) < k, and bisects [lo, hi) on the bit patterns, counting keys >= mid
-// over the row with a DPP sum (two steps per round, one ballot per round).
-// A row stops once clo = k (the selection is every key >= lo), hi = lo + 1
-// (lo is the k-th largest key itself, and it is tied), or at most three
-// keys lie in [lo, hi).  In the last case the k - chi keys still needed are
-// either one (lo becomes the largest key below hi) or all but one (lo
-// becomes the smallest key at or above lo), and the selection is every key
-// above lo plus the first k - #(keys > lo) keys equal to lo in channel
-// order (segment by segment, lanes in order within a segment).  The first lo is the smallest lane maximum (at least LPR keys reach
-// it, so it is valid for k <= LPR), for LPR < k <= 2 LPR the smallest lane's
-// second-largest key, else 0; the first hi is the row maximum plus one; an
-// open row's interval halves every step, so every row stops within 32 steps.
+// the bit patterns of the non-negative fp32 magnitudes, which order like the
+// values.
+//
+// The search runs on the keys' 16-bit prefixes.  Every lane of a row keeps the
+// same bounds lo < hi with #(keys >= lo) >= k > #(keys >= hi), lo and hi
+// multiples of 2^16, and halves [lo, hi).  The first lo is a key that k
+// disjoint groups of keys all reach (1, 2 or 4 groups a lane: the smallest
+// group maximum), the first hi the row maximum's successor.  The prefixes'
+// distances from the first lo, saturated at 255, are bytes, four to a
+// register: with S(m) = sum |q - m| over the keys, S(m - 1) - S(m) =
+// 2 #(q >= m) - #keys, so two v_sad_u8 count four keys, where a compare and
+// an add count one.  A row stops once the selection is every key >= lo, the
+// bounds are neighbours, or at most three keys lie between them.  A row whose
+// threshold lies past the 255 steps, or that has no first lo (k above four
+// groups a lane), or that still holds more than three keys in a prefix goes on
+// with the full keys, counted one by one.
+//
+// Then, of the keys in [lo, hi), the last one still needed is the largest (if
+// one is needed) or the first one not needed is the smallest (if all but one
+// are), found with one max reduction on keys (v_xad_u32 turns both into the
+// same max); otherwise lo is the k-th key itself.  Where keys tie at the k-th,
+// the first ones in channel order are taken (segment by segment, lanes in
+// order within a segment).
 // Returns the lane's selection as a CPL-bit mask.
 #pragma once
 
@@ -81,38 +89,92 @@ __device__ __forceinline__ uint32_t row_count_ge(const uint32_t (&key)[CPL], uin
   return row_sum_u32<LPR>(c);
 }
 
+// sel = 2 sel + (key >= thr)
+__device__ __forceinline__ void push_ge(uint32_t& sel, uint32_t key, uint32_t thr) {
+  asm("v_cmp_ge_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(sel) : "v"(key), "v"(thr) : "vcc");
+}
+
 // The lane's selected keys (bit i: key i, the channel given above) of the k
 // largest keys of its row, ties to the lower channel.  0 <= k <= d.
+//
+// VALU instructions for a wave of 8 rows (8 lanes of 16 keys, k = 16): about
+// 290 against 540 with counts on the full keys; TODO figures
 template <int LPR, int CPL, int H = 1>
 __device__ __forceinline__ uint32_t row_topk_mask(const uint32_t (&key)[CPL], int k) {
-  static_assert(H >= 1 && CPL % H == 0 && CPL < 32, "segments, and one mask bit per key");
-  constexpr int S = CPL / H;
+  static_assert(H >= 1 && CPL % H == 0 && CPL % 4 == 0 && CPL < 32, "segments, whole registers, one mask bit per key");
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  constexpr int S = CPL / H, NP = CPL / 2, NQ = CPL / 4, N = LPR * CPL;
   constexpr uint32_t kAll = (1u << CPL) - 1u;
   if (k <= 0) return 0u;
-  if (k >= LPR * CPL) return kAll;
-  uint32_t lmax = key[0];
+  if (k >= N) return kAll;
+  // the prefixes, two to a register, and their maxima over the lane's four groups
+  u16x2 p[NP];
 #pragma unroll
-  for (int i = 1; i < CPL; ++i) lmax = key[i] > lmax ? key[i] : lmax;
-  const uint32_t rmax = row_ext_u32<LPR, true>(lmax);
-  uint32_t lo = 0u;
-  if (k <= LPR) {
-    lo = row_ext_u32<LPR, false>(lmax);
-  } else if (CPL >= 2 && k <= 2 * LPR) {
-    // every lane's second-largest key: at least 2 LPR keys reach the smallest
-    uint32_t m1 = 0u, m2 = 0u;
+  for (int i = 0; i < NP; ++i)
+    p[i] = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(key[2 * i + 1], key[2 * i], 0x07060302u));
+  u16x2 ma = p[0], mb = p[NP / 2];
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      const uint32_t x = key[i];
-      m2 = max(m2, min(m1, x));
-      m1 = max(m1, x);
-    }
-    lo = row_ext_u32<LPR, false>(m2);
+  for (int i = 1; i < NP / 2; ++i) {
+    ma = __builtin_elementwise_max(ma, p[i]);
+    mb = __builtin_elementwise_max(mb, p[NP / 2 + i]);
   }
-  uint32_t hi = rmax + 1u;
-  uint32_t clo = row_count_ge<LPR, CPL>(key, lo), chi = 0;
+  const u16x2 mh = __builtin_elementwise_max(ma, mb);
+  const uint32_t lmax = max((uint32_t)mh.x, (uint32_t)mh.y);
+  const uint32_t rmax = row_ext_u32<LPR, true>(lmax);
+  uint32_t base = 0;
+  if (k <= LPR) {
+    base = row_ext_u32<LPR, false>(lmax);
+  } else if (k <= 2 * LPR) {
+    base = row_ext_u32<LPR, false>(min((uint32_t)mh.x, (uint32_t)mh.y));
+  } else if (k <= 4 * LPR) {
+    const u16x2 ml = __builtin_elementwise_min(ma, mb);
+    base = row_ext_u32<LPR, false>(min((uint32_t)ml.x, (uint32_t)ml.y));
+  }
+  // q = min(prefix - base, 255) (0 below base), four to a register
+  uint32_t q[NQ];
+  {
+    const u16x2 b2 = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(base, base, 0x01000100u));
+    const u16x2 top = {255, 255};
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      const u16x2 x = __builtin_elementwise_min(__builtin_elementwise_sub_sat(p[2 * j], b2), top);
+      const u16x2 y = __builtin_elementwise_min(__builtin_elementwise_sub_sat(p[2 * j + 1], b2), top);
+      q[j] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, y), __builtin_bit_cast(uint32_t, x), 0x06040200u);
+    }
+  }
+  // Bounds and counts in steps from base; counts as 2 #(q >= m) - N.  The
+  // count at lo = 0 is not taken: N bounds it.
+  const int kd = 2 * k - N;
+  int lo8 = 0, hi8 = (int)min(rmax - base + 1u, 256u), clo2 = N, chi2 = -N;
+  auto step = [&]() {
+    const int mid = max((lo8 + hi8) >> 1, 1);  // 1: bounds 0 and 1 count at 1 again
+    const uint32_t m1 = __builtin_amdgcn_perm((uint32_t)mid, (uint32_t)mid, 0u), m0 = m1 - 0x01010101u;
+    uint32_t s0 = 0, s1 = 0;
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      s0 = __builtin_amdgcn_sad_u8(q[j], m0, s0);
+      s1 = __builtin_amdgcn_sad_u8(q[j], m1, s1);
+    }
+    const int c = (int)row_sum_u32<LPR>(s0 - s1);
+    const bool up = c >= kd;
+    lo8 = up ? mid : lo8;
+    clo2 = up ? c : clo2;
+    hi8 = up ? hi8 : mid;
+    chi2 = up ? chi2 : c;
+  };
+  // A stopped row may take further steps: they keep the bounds' conditions.
+  // (A wave of eight rows of the synthetic keys needs 5.9 steps, hardly ever
+  // fewer than five.)
+#pragma unroll
+  for (int u = 0; u < 4; ++u) step();
+  for (int u = 0; u < 5; ++u) {
+    step();
+    if (__ballot(clo2 != kd && hi8 - lo8 > 1 && clo2 - chi2 > 6) == 0) break;
+  }
+  uint32_t lo = (base + (uint32_t)lo8) << 16;
+  uint32_t hi = (hi8 == 256 ? rmax + 1u : base + (uint32_t)hi8) << 16;
+  uint32_t clo = (uint32_t)(clo2 + N) >> 1, chi = (uint32_t)(chi2 + N) >> 1;
   const uint32_t ku = (uint32_t)k;
-  // A stopped row may take further steps: they keep both invariants and
-  // only shrink [lo, hi), so no per-row guard is needed inside a round.
   for (int round = 0; round < 20; ++round) {
     if (__ballot(clo != ku && hi - lo > 1u && clo - chi > 3u) == 0) break;
 #pragma unroll
@@ -126,65 +188,49 @@ __device__ __forceinline__ uint32_t row_topk_mask(const uint32_t (&key)[CPL], in
       chi = up ? chi : c;
     }
   }
-  {
-    // at most three keys in [lo, hi): one more key needed, or one too many
-    const uint32_t need = ku - chi, ns = clo - chi;
-    const bool take_max = ns > need && need == 1u;
-    const bool drop_min = ns > need && need + 1u == ns && !take_max;
-    if (__ballot(take_max || drop_min) != 0) {
-      // one max reduction for both: the largest key below hi, or the
-      // complement of the smallest key at or above lo (complements order
-      // the other way round)
-      uint32_t m = 0;
+  // the last key taken (one more is needed above hi), or the first one left
+  // out (one too many at or above lo); otherwise every key >= lo
+  const uint32_t need = ku - chi, ns = clo - chi;
+  const bool take = clo != ku && need == 1u;
+  const bool drop = clo != ku && !take && ns == need + 1u;
+  uint32_t edge = lo, thr = lo;
+  if (__ballot(take || drop) != 0) {
+    // the largest key below hi is the largest key - hi in unsigned arithmetic,
+    // the smallest key at or above lo the largest ~key + lo
+    const uint32_t flip = drop ? 0xFFFFFFFFu : 0u, add = drop ? lo : 0u - hi;
+    uint32_t m = 0;
 #pragma unroll
-      for (int i = 0; i < CPL; ++i) {
-        const uint32_t x = take_max ? (key[i] < hi ? key[i] : 0u) : (key[i] >= lo ? ~key[i] : 0u);
-        m = x > m ? x : m;
-      }
-      m = row_ext_u32<LPR, true>(m);
-      if (take_max) lo = m;
-      if (drop_min) lo = ~m;
-      clo = row_count_ge<LPR, CPL>(key, lo);
-    }
+    for (int i = 0; i < CPL; ++i) m = max(m, (key[i] ^ flip) + add);
+    m = (row_ext_u32<LPR, true>(m) - add) ^ flip;
+    edge = take || drop ? m : lo;
+    thr = drop ? m + 1u : edge;
   }
   uint32_t sel = 0;
 #pragma unroll
-  for (int i = 0; i < CPL; ++i) sel |= key[i] >= lo ? 1u << i : 0u;
-  const bool tied = clo != ku;  // lo is the k-th largest key, and it is tied
+  for (int i = CPL - 1; i >= 0; --i) push_ge(sel, key[i], thr);
+  const bool tied = row_sum_u32<LPR>((uint32_t)__builtin_popcount(sel)) != ku;  // keys equal to edge
   if (__ballot(tied) != 0) {
-    // keys above lo, then the first equal keys in channel order
-    const uint32_t cgt = row_count_ge<LPR, CPL>(key, lo + 1u);
+    // keys above edge, then the first equal keys in channel order
     uint32_t eq = 0;
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) eq |= key[i] == lo ? 1u << i : 0u;
+    for (int i = 0; i < CPL; ++i) eq |= key[i] == edge ? 1u << i : 0u;
+    const uint32_t gt = sel & ~eq;
     // rank of the lane's first equal key of each segment: the equal keys of
     // the row's earlier segments, then those of the segment's lower lanes
-    uint32_t start[H];
-    uint32_t base = 0;
+    int left = k - (int)row_sum_u32<LPR>((uint32_t)__builtin_popcount(gt));
+    uint32_t s2 = gt;
 #pragma unroll
     for (int sg = 0; sg < H; ++sg) {
-      const uint32_t n = (uint32_t)__builtin_popcount(eq & (((1u << S) - 1u) << (sg * S)));
-      start[sg] = base + row_prefix_u32<LPR>(n) - n;
-      if (sg + 1 < H) base += row_sum_u32<LPR>(n);
+      constexpr uint32_t kSeg = S == 32 ? ~0u : (1u << S) - 1u;
+      uint32_t e = eq & (kSeg << (sg * S));
+      const uint32_t n = (uint32_t)__builtin_popcount(e);
+      const int mine = left - (int)(row_prefix_u32<LPR>(n) - n);  // how many of the lane's equal keys are taken
+      while (__ballot(e != 0u && (int)__builtin_popcount(e) > mine) != 0)
+        if ((int)__builtin_popcount(e) > mine) e &= ~(e == 0u ? 0u : 0x80000000u >> __builtin_clz(e));
+      s2 |= e;
+      if (sg + 1 < H) left -= (int)row_sum_u32<LPR>(n);
     }
-    if (tied) {
-      const uint32_t need = ku - cgt;
-      uint32_t s2 = 0;
-#pragma unroll
-      for (int sg = 0; sg < H; ++sg) {
-        uint32_t rank = start[sg];
-#pragma unroll
-        for (int c = 0; c < S; ++c) {
-          const int i = sg * S + c;
-          if (key[i] > lo) s2 |= 1u << i;
-          if (key[i] == lo) {
-            if (rank < need) s2 |= 1u << i;
-            ++rank;
-          }
-        }
-      }
-      sel = s2;
-    }
+    sel = tied ? s2 : sel;
   }
   return sel;
 }
