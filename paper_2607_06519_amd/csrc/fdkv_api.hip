@@ -165,6 +165,33 @@ ProbeWs probe_ws_layout(const fdkv_dims* d, int T) {
   return w;
 }
 
+// Workgroups per unit of a deviation Gram launch, and the tokens of each.  A
+// launch of `units` units of `steps` steps runs in rounds of as many
+// workgroups as the chip holds: `at_once`, 256 CUs times those that a CU holds
+// (two of pairs, by registers; one of blocks of four, by LDS).  Of the counts
+// that the workspace holds partials for, the one of the least cost is taken:
+// the steps over all rounds, a workgroup's start and its contraction with the
+// probe Gram matrix counted as a step, plus a quarter of a workgroup's steps,
+// as they don't end together.  Against 1024 tokens a workgroup on the 8B shape
+// in the default block setting at 12345 tokens (48 units of four: 624
+// workgroups, the third round nearly empty) the probe takes 638 in place of 705 us;
+// where the rounds come out even it stays within 2% (8B pairs, 32768 tokens:
+// 834 and 845 us).
+void probe_split(ProbeParams* p, int units, int T, int bsize, int row_bytes, int cap) {
+  const int rows = probe_rows(bsize, row_bytes), at_once = 256 * (bsize == 2 ? 2 : 1);
+  const int64_t steps = (T + rows - 1) / rows;
+  int64_t best = INT64_MAX;
+  for (int n = 1; n <= cap; ++n) {
+    const int64_t each = (steps + n - 1) / n, used = (steps + each - 1) / each;
+    const int64_t cost = 4 * ((units * used + at_once - 1) / at_once) * (each + 1) + each;
+    if (cost <= best) {
+      best = cost;
+      p->chunk_tokens = (int)(each * rows);
+      p->n_chunks = (int)used;
+    }
+  }
+}
+
 uint64_t decode_chunks(int max_T) { return (uint64_t)(max_T + kDecodeWgTokens - 1) / kDecodeWgTokens; }
 
 // The split-K records of fdkv_decode_attn_static live in this file-scope
@@ -452,12 +479,14 @@ fdkv_status fdkv_probe(const fdkv_dims* dims, int32_t seq_len, const void* const
   pp.d = dims->head_dim;
   pp.topk = dims->topk;
   pp.n_probe = n_probe;
-  pp.n_chunks = (int)probe_chunks(seq_len);
+  pp.max_chunks = (int)probe_chunks(seq_len);
   pp.bf16 = dims->dtype != FDKV_F32;
   for (int B = 2; B <= 4; B += 2) {
     pp.bl = blocks_of_size(sch, B);
     pp.bsize = B;
     if (pp.bl.n == 0) continue;
+    probe_split(&pp, pp.bl.n * pp.hkv, seq_len, B, (int)row_bytes, pp.max_chunks);
+    pp.used_chunks[B == 4] = pp.n_chunks;
     const hipError_t e = launch_probe(pp, s);  // every block takes its top-k inside its Gram kernel
     if (e != hipSuccess) return hip_fail(e, "probe");
   }

@@ -158,20 +158,26 @@ struct AppendParams {
 };
 
 // probe
-constexpr int kProbeStep = 128;     // tokens per MFMA step
-constexpr int kProbeChunk = 1024;   // tokens per probe workgroup
+constexpr int kProbeChunk = 1024;   // the workspace holds a partial per this many tokens of a unit
+// tokens per step of the deviation Gram kernels
+__host__ __device__ constexpr int probe_rows(int bsize, int row_bytes) {
+  return bsize == 2 || 512 / (row_bytes / 16) > 32 ? 64 : 32;
+}
 
 struct ProbeParams {
   const void* k[kMaxPtrLayers];
   const void* qp[kMaxPtrLayers];
   float* gram_q;               // [layers][hkv][d][d]  sums of q q^T over probe rows (see probe.hip)
-  float* partial;              // [units][n_chunks][2]
+  float* partial;              // [units][max_chunks][2]
   float* errors;               // [units][2]
   uint8_t* ksel;               // out: the K selections (selection_offset), or null
   int ksel_bytes;              // bytes per piece of ksel (1, or 4 with blocks of four)
   BlockList bl;                // blocks of size bsize
   int8_t bsizes[kMaxBlocks];   // every block's size (finalize)
-  int seq_len, bsize, n_blocks, hkv, hq, d, topk, n_probe, n_chunks;
+  int seq_len, bsize, n_blocks, hkv, hq, d, topk, n_probe;
+  int chunk_tokens, n_chunks;  // this launch: tokens per workgroup, workgroups per unit
+  int max_chunks;              // partials of a unit in the workspace
+  int used_chunks[2];          // partials written per unit: pairs, blocks of four (finalize)
   bool bf16;
 };
 

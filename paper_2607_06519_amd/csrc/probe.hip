@@ -76,19 +76,35 @@ struct TriTiles {
   }
 };
 
-// Operand of v_mfma_f32_32x32x16_bf16 for channel block I and rows
-// 16kk .. 16kk+15 of a row-major bf16 tile with LDR elements per row: lane l
-// gets channel 32I + l%32 of rows 16kk + 8(l/32) .. +7, from two transposing
-// reads.  In each 16-lane group, lane i of ds_read_b64_tr_b16 returns element
-// i%4 of the 4-element row addressed by lane 4j + i/4 as its element j; the
-// lanes therefore address rows base + i/4 at channels 32I + 16g + 4(i%4).
-template <int LDR>
-__device__ __forceinline__ bf16x8_t gram_operand(const uint16_t* tile, int kk, int I, int lane) {
+// The LDS tiles of the Gram kernels: row-major bf16 rows of D elements, the
+// 64-byte blocks of a row (32 channels) permuted by the row so that the four
+// rows and two 32-byte halves that 32 lanes of a transposing read touch lie in
+// distinct banks.  (Rows padded by 32 bytes instead cost two conflict cycles a
+// read: 40% of what the reads themselves took.)  Element of channel c of a row:
+template <int D>
+__device__ __forceinline__ int tile_at(int row, int c) {
+  const int s = D == 128 ? row & 3 : (row >> 1) & 1;
+  return row * D + ((((c >> 5) ^ s) << 5) | (c & 31));
+}
+
+// Operand of v_mfma_f32_32x32x16_bf16 for a channel block and rows
+// 16kk .. 16kk+15 of a tile: lane l gets channel 32I + l%32 of rows
+// 16kk + 8(l/32) .. +7, from two transposing reads.  In each 16-lane group,
+// lane i of ds_read_b64_tr_b16 returns element i%4 of the 4-element row
+// addressed by lane 4j + i/4 as its element j; the lanes therefore address rows
+// base + i/4 at channels 32I + 16g + 4(i%4).  `at` is the lane's element for
+// kk = 0 (operand_at; block I of it is operand_at(0) ^ 32 I).
+template <int D>
+__device__ __forceinline__ int operand_at(int I, int lane) {
   const int h = lane >> 5, g = (lane >> 4) & 1, li = lane & 15;
-  const int row = 16 * kk + 8 * h + (li >> 2);
-  const int col = 32 * I + 16 * g + 4 * (li & 3);
-  const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + row * LDR + col));
-  const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (row + 4) * LDR + col));
+  return tile_at<D>(8 * h + (li >> 2), 16 * g + 4 * (li & 3)) ^ (32 * I);
+}
+template <int D>
+__device__ __forceinline__ bf16x8_t gram_operand(const uint16_t* tile, int kk, int at) {
+  // rows 16 kk + 4 j further keep the permutation at D = 128; at D = 64 four rows further flip
+  // nothing either (bit 1 of the row is kept)
+  const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + 16 * kk * D + at));
+  const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (16 * kk + 4) * D + at));
   const i16x8_t v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   return __builtin_bit_cast(bf16x8_t, v);
 }
@@ -198,10 +214,10 @@ __global__ __launch_bounds__(256) void probe_qgram_mfma_kernel(ProbeParams P) {
   constexpr int NPc = D / 8;                     // 16-byte pieces per row
   constexpr int NB = D / 32, NT = NB * (NB + 1) / 2;
   constexpr int TPW = (NT + 3) / 4;              // blocks per wave
-  constexpr int R = kGramRows, LDR = D + 16;     // rows per step, LDS row stride (elements)
+  constexpr int R = kGramRows;                   // rows per step
   constexpr int LPT = R * NPc / 256;             // loads per thread per step
   constexpr TriTiles<NB> tri{};
-  __shared__ __attribute__((aligned(16))) uint16_t tile[R * LDR];
+  __shared__ __attribute__((aligned(256))) uint16_t tile[R * D];
   const GramSlot gs = gram_slot(P, blockIdx.x);
   const int head = gs.head;
   const int G = P.hq / P.hkv, NP = P.n_probe;
@@ -231,7 +247,7 @@ __global__ __launch_bounds__(256) void probe_qgram_mfma_kernel(ProbeParams P) {
 #pragma unroll
     for (int j = 0; j < LPT; ++j) {
       const int i = tid + 256 * j;
-      *reinterpret_cast<uint4*>(&tile[(i / NPc) * LDR + (i % NPc) * 8]) = buf[j];
+      *reinterpret_cast<uint4*>(&tile[tile_at<D>(i / NPc, (i % NPc) * 8)]) = buf[j];
     }
     load(r0 + R);
     __syncthreads();
@@ -239,7 +255,7 @@ __global__ __launch_bounds__(256) void probe_qgram_mfma_kernel(ProbeParams P) {
     for (int kk = 0; kk < R / 16; ++kk) {
       bf16x8_t op[NB];
 #pragma unroll
-      for (int I = 0; I < NB; ++I) op[I] = gram_operand<LDR>(tile, kk, I, lane);
+      for (int I = 0; I < NB; ++I) op[I] = gram_operand<D>(tile, kk, operand_at<D>(I, lane));
 #pragma unroll
       for (int t = 0; t < NT; ++t)  // block t belongs to wave t / TPW (indices stay compile-time)
         if (t / TPW == wave) acc[t % TPW] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[tri.i[t]], op[tri.j[t]], acc[t % TPW], 0, 0, 0);
@@ -271,13 +287,12 @@ __global__ __launch_bounds__(256) void probe_qgram_mfma_kernel(ProbeParams P) {
 // so four waves fit on a SIMD for the VALU-heavy selection.  The next step's
 // loads are in flight during the MFMAs.
 template <int D, bool BF16>
-__global__ __launch_bounds__(512) void probe_dgram_kernel(ProbeParams P) {
+__global__ __launch_bounds__(512, BF16 ? 4 : 2) void probe_dgram_kernel(ProbeParams P) {
   constexpr int E = BF16 ? 2 : 4;
   constexpr int NPc = D * E / 16;                // 16-byte input pieces per row
   constexpr int CPP = 16 / E;                    // channels per piece
-  constexpr int NB = D / 32, NT = NB * (NB + 1) / 2;
-  constexpr int WPM = 4, TPW = (NT + WPM - 1) / WPM;  // four waves per matrix: block t on wave t % WPM
-  constexpr int R = kGramRows, LDR = D + 16;
+  constexpr int TPW = D == 128 ? 3 : 1;          // blocks per wave at most
+  constexpr int R = probe_rows(2, D * E);
   constexpr int LPT = R * NPc / 512;             // loads per thread per layer per step
   // a thread holds PPT pieces of one token row, one from each of its PPT
   // runs of LPR = NPc / PPT pieces (at least 8 lanes, at most 16 keys a lane:
@@ -287,9 +302,8 @@ __global__ __launch_bounds__(512) void probe_dgram_kernel(ProbeParams P) {
   constexpr int PPT = PPT0 < 16 / CPP ? PPT0 : 16 / CPP;
   constexpr int LPR = NPc / PPT, KPT = PPT * CPP;
   static_assert(PPT >= 1 && LPT % PPT == 0 && LPR >= 8, "row layout");
-  constexpr TriTiles<NB> tri{};
   // [D hi, D lo, Dbar hi, Dbar lo][token][channel]
-  __shared__ __attribute__((aligned(16))) uint16_t tile[4][R * LDR];
+  __shared__ __attribute__((aligned(256))) uint16_t tile[4][R * D];
   __shared__ float red[8];
 
   const int chunk = blockIdx.x;
@@ -297,14 +311,24 @@ __global__ __launch_bounds__(512) void probe_dgram_kernel(ProbeParams P) {
   const int first = P.bl.first[bi];
   const int unit = P.bl.block[bi] * P.hkv + head;
   const int T = P.seq_len, k = P.topk;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const uint64_t RB = (uint64_t)D * E;
   const uint64_t plane = (uint64_t)T * RB;
   const auto ka = make_rsrc(static_cast<const uint8_t*>(P.k[first]) + (uint64_t)head * plane, plane);
   const auto kb = make_rsrc(static_cast<const uint8_t*>(P.k[first + 1]) + (uint64_t)head * plane, plane);
-  const int t_begin = chunk * kProbeChunk;
-  const int t_end = min(T, t_begin + kProbeChunk);
-  const int mat = wave >> 2;                      // 0: D, 1: Dbar
+  const int t_begin = min(T, chunk * P.chunk_tokens);
+  const int t_end = min(T, t_begin + P.chunk_tokens);
+  // Four waves per matrix (0: D, 1: Dbar), which share operands: of the ten
+  // blocks at D = 128 waves 0 and 1 take those of channel blocks {0, 1} and
+  // {2, 3} among themselves, (X, Y), (X, X) and (Y, Y), waves 2 and 3 those of
+  // block 0 or 1 with {2, 3}, (X, Y) and (X, Z): ten operands read where a
+  // round-robin of the blocks reads all four for each wave.  (The LDS reads
+  // bound this phase.)  At D = 64 waves 0-2 take (X, Y) = (0, 0), (0, 1), (1, 1).
+  const int mat = wave >> 2, w4 = wave & 3;
+  const bool diag = w4 < 2;
+  const int X = D == 64 ? w4 >> 1 : diag ? 2 * w4 : w4 - 2;
+  const int Y = D == 64 ? (w4 + 1) >> 1 : diag ? 2 * w4 + 1 : 2;
+  const int at_x = operand_at<D>(X, lane), at_y = operand_at<D>(Y, lane), at_z = operand_at<D>(3, lane);
 
   f32x16_t acc[TPW];
 #pragma unroll
@@ -323,6 +347,7 @@ __global__ __launch_bounds__(512) void probe_dgram_kernel(ProbeParams P) {
       rb[j] = load16(kb, ok ? (uint32_t)(t * RB + pc * 16) : kOobOff);
     }
   };
+  uint8_t* ksel_unit = P.ksel + selection_offset(unit, T, t_begin, 0, D, E, P.ksel_bytes);
   load(t_begin);
   for (int t0 = t_begin; t0 < t_end; t0 += R) {
 #pragma unroll
@@ -355,13 +380,11 @@ __global__ __launch_bounds__(512) void probe_dgram_kernel(ProbeParams P) {
       // Dbar: drop the thread's channels that are among the token's top-k
       const uint32_t sel = row_topk_mask<LPR, KPT, PPT>(key, k);
       const uint32_t keep = ~sel & ((1u << KPT) - 1u);
-      if (P.ksel) {  // the selection, for compress to reuse
-        const int t = t0 + row;
-        if (t < t_end)
+      if (P.ksel && t0 + row < t_end) {  // the selection, for compress to reuse
+        uint8_t* out = ksel_unit + ((uint32_t)(t0 - t_begin + row) * NPc + lr) * (uint32_t)P.ksel_bytes;
 #pragma unroll
-          for (int h = 0; h < PPT; ++h)
-            P.ksel[selection_offset(unit, T, t, h * LPR + lr, D, E, P.ksel_bytes)] =
-                (uint8_t)((sel >> (h * CPP)) & ((1u << CPP) - 1u));
+        for (int h = 0; h < PPT; ++h)
+          out[h * LPR * P.ksel_bytes] = (uint8_t)((sel >> (h * CPP)) & ((1u << CPP) - 1u));
       }
       uint32_t wd[KPT / 2], wl[KPT / 2], wr[KPT / 2], wrl[KPT / 2];
 #pragma unroll
@@ -377,7 +400,7 @@ __global__ __launch_bounds__(512) void probe_dgram_kernel(ProbeParams P) {
       for (int m = 0; m < 4; ++m)
 #pragma unroll
         for (int h = 0; h < PPT; ++h) {
-          uint16_t* dst = &tile[m][row * LDR + (h * LPR + lr) * CPP];
+          uint16_t* dst = &tile[m][tile_at<D>(row, (h * LPR + lr) * CPP)];
           const uint32_t* sp = src[m] + h * (CPP / 2);
           if constexpr (CPP == 8)
             *reinterpret_cast<uint4*>(dst) = make_uint4(sp[0], sp[1], sp[2], sp[3]);
@@ -387,22 +410,27 @@ __global__ __launch_bounds__(512) void probe_dgram_kernel(ProbeParams P) {
     }
     load(t0 + R);
     __syncthreads();
+    const uint16_t* th = tile[2 * mat];
+    const uint16_t* tl = tile[2 * mat + 1];
+    auto mfma3 = [](const bf16x8_t& ih, const bf16x8_t& il, const bf16x8_t& jh, const bf16x8_t& jl, f32x16_t& a) {
+      a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ih, jh, a, 0, 0, 0);
+      a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ih, jl, a, 0, 0, 0);
+      a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(il, jh, a, 0, 0, 0);
+    };
 #pragma unroll
     for (int kk = 0; kk < R / 16; ++kk) {
-      bf16x8_t oh[NB], ol[NB];
-#pragma unroll
-      for (int I = 0; I < NB; ++I) {
-        oh[I] = gram_operand<LDR>(tile[2 * mat], kk, I, lane);
-        ol[I] = gram_operand<LDR>(tile[2 * mat + 1], kk, I, lane);
-      }
-#pragma unroll
-      for (int t = 0; t < NT; ++t)  // indices stay compile-time
-        if (t % WPM == (wave & 3)) {
-          const int bi_ = tri.i[t], bj_ = tri.j[t];
-          f32x16_t a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(oh[bi_], oh[bj_], acc[t / WPM], 0, 0, 0);
-          a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(oh[bi_], ol[bj_], a, 0, 0, 0);
-          acc[t / WPM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ol[bi_], oh[bj_], a, 0, 0, 0);
+      const bf16x8_t xh = gram_operand<D>(th, kk, at_x), xl = gram_operand<D>(tl, kk, at_x);
+      const bf16x8_t yh = gram_operand<D>(th, kk, at_y), yl = gram_operand<D>(tl, kk, at_y);
+      mfma3(xh, xl, yh, yl, acc[0]);
+      if constexpr (D == 128) {
+        if (diag) {
+          mfma3(xh, xl, xh, xl, acc[1]);
+          mfma3(yh, yl, yh, yl, acc[2]);
+        } else {
+          const bf16x8_t zh = gram_operand<D>(th, kk, at_z), zl = gram_operand<D>(tl, kk, at_z);
+          mfma3(xh, xl, zh, zl, acc[1]);
         }
+      }
     }
     __syncthreads();
   }
@@ -410,22 +438,22 @@ __global__ __launch_bounds__(512) void probe_dgram_kernel(ProbeParams P) {
   // < C, S_u >, off-diagonal blocks counted twice (both matrices symmetric)
   const float* S = gram_at(P, first, head);
   float part = 0.f;
+  auto contract = [&](const f32x16_t& a, int bi_, int bj_) {
+    const float wgt = bi_ == bj_ ? 1.f : 2.f;
+    const float* Sb = S + (32 * bi_ + 4 * (lane >> 5)) * D + 32 * bj_ + (lane & 31);
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    if (t % WPM != (wave & 3)) continue;
-    const float wgt = (tri.i[t] == tri.j[t]) ? 1.f : 2.f;
-    const int col = 32 * tri.j[t] + (lane & 31);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = 32 * tri.i[t] + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      part = fmaf(wgt * acc[t / WPM][r], S[row * D + col], part);
-    }
+    for (int r = 0; r < 16; ++r) part = fmaf(wgt * a[r], Sb[(8 * (r >> 2) + (r & 3)) * D], part);
+  };
+  if (D == 128 || w4 < 3) contract(acc[0], X, Y);
+  if constexpr (D == 128) {
+    contract(acc[1], X, diag ? X : 3);
+    if (diag) contract(acc[2], Y, Y);
   }
   part = wave_sum(part);
   if (lane == 0) red[wave] = part;
   __syncthreads();
   if (tid < 2)
-    P.partial[((uint64_t)unit * P.n_chunks + chunk) * 2 + tid] =
+    P.partial[((uint64_t)unit * P.max_chunks + chunk) * 2 + tid] =
         (red[4 * tid] + red[4 * tid + 1]) + (red[4 * tid + 2] + red[4 * tid + 3]);
 }
 
@@ -446,14 +474,12 @@ __global__ __launch_bounds__(512) void probe_dgram4_kernel(ProbeParams P) {
   constexpr int NPc = D * E / 16;                // 16-byte input pieces per row
   constexpr int CPP = 16 / E;                    // channels per piece
   constexpr int NB = D / 32, NT = NB * (NB + 1) / 2;
-  // LDS rows padded by 16 channels (8 at d = 64, where 16 tiles of 64 rows
-  // would pass the 160 KB of a workgroup)
-  constexpr int R = 512 / NPc > 32 ? 512 / NPc : 32, LDR = D == 64 ? D + 8 : D + 16;
+  constexpr int R = probe_rows(4, D * E);
   constexpr int LPT = R * NPc / 512;             // pieces per thread per step
   constexpr TriTiles<NB> tri{};
   static_assert(LPT >= 1 && R % 16 == 0, "shape");
   // [layer * 2 + residual][hi, lo][token][channel]
-  __shared__ __attribute__((aligned(16))) uint16_t tile[16][R * LDR];
+  __shared__ __attribute__((aligned(256))) uint16_t tile[16][R * D];
   __shared__ float red[8];
 
   const int chunk = blockIdx.x;
@@ -461,17 +487,14 @@ __global__ __launch_bounds__(512) void probe_dgram4_kernel(ProbeParams P) {
   const int first = P.bl.first[bi];
   const int unit = P.bl.block[bi] * P.hkv + head;
   const int T = P.seq_len, k = P.topk;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const uint64_t RB = (uint64_t)D * E;
   const uint64_t plane = (uint64_t)T * RB;
   __amdgpu_buffer_rsrc_t kr[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n) kr[n] = make_rsrc(static_cast<const uint8_t*>(P.k[first + n]) + (uint64_t)head * plane, plane);
-  const int t_begin = chunk * kProbeChunk;
-  const int t_end = min(T, t_begin + kProbeChunk);
-  const float F1[4] = {kDct4A, kDct4B, -kDct4B, -kDct4A};   // F_4[1][p]
-  const float F2[4] = {0.5f, -0.5f, -0.5f, 0.5f};           // F_4[2][p]
-  const float F3[4] = {kDct4B, -kDct4A, kDct4A, -kDct4B};   // F_4[3][p]
+  const int t_begin = min(T, chunk * P.chunk_tokens);
+  const int t_end = min(T, t_begin + P.chunk_tokens);
 
   f32x16_t acc[NT];
 #pragma unroll
@@ -530,22 +553,29 @@ __global__ __launch_bounds__(512) void probe_dgram4_kernel(ProbeParams P) {
           float z1, z2, z3;  // evaluated again (the same rounded operations): fewer live registers
           dct4_high(x[0], x[1], x[2], x[3], z1, z2, z3);
           const float m = ((x[0] + x[3]) + (x[1] + x[2])) * 0.25f;
-          const float k1 = (kept >> (3 * c)) & 1u ? z1 : 0.f;
-          const float k2 = (kept >> (3 * c + 1)) & 1u ? z2 : 0.f;
-          const float k3 = (kept >> (3 * c + 2)) & 1u ? z3 : 0.f;
+          // what the residual reconstruction misses: the images of the
+          // coefficients that are not kept.  F_4's columns mirror each other
+          // (layers 0 and 3, 1 and 2): with u = a Z_1 + b Z_3,
+          // v = b Z_1 - a Z_3, w = Z_2 / 2 the layers' images are w + u,
+          // v - w, -v - w, w - u, and the deviations (mean less layer) their
+          // negatives.
+          const float k1 = (kept >> (3 * c)) & 1u ? 0.f : z1;
+          const float k2 = (kept >> (3 * c + 1)) & 1u ? 0.f : z2;
+          const float k3 = (kept >> (3 * c + 2)) & 1u ? 0.f : z3;
+          const float u = fmaf(kDct4A, k1, kDct4B * k3), v = fmaf(kDct4B, k1, -(kDct4A * k3));
 #pragma unroll
-          for (int n = 0; n < 4; ++n) {
-            const float dev = m - x[n];
-            dv[2 * n][e] = dev;
-            dv[2 * n + 1][e] = dev + (F1[n] * k1 + F2[n] * k2 + F3[n] * k3);
-          }
+          for (int n = 0; n < 4; ++n) dv[2 * n][e] = m - x[n];
+          dv[1][e] = fmaf(-0.5f, k2, -u);
+          dv[3][e] = fmaf(0.5f, k2, -v);
+          dv[5][e] = fmaf(0.5f, k2, v);
+          dv[7][e] = fmaf(-0.5f, k2, u);
         }
 #pragma unroll
         for (int mt = 0; mt < 8; ++mt) split_bf16x2(dv[mt][0], dv[mt][1], hw[2 * mt][c2 >> 1], hw[2 * mt + 1][c2 >> 1]);
       }
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
-        uint16_t* dst = &tile[m][row * LDR + pc * CPP];
+        uint16_t* dst = &tile[m][tile_at<D>(row, pc * CPP)];
         if constexpr (CPP == 8)
           *reinterpret_cast<uint4*>(dst) = make_uint4(hw[m][0], hw[m][1], hw[m][2], hw[m][3]);
         else
@@ -559,8 +589,8 @@ __global__ __launch_bounds__(512) void probe_dgram4_kernel(ProbeParams P) {
       bf16x8_t oh[NB], ol[NB];
 #pragma unroll
       for (int I = 0; I < NB; ++I) {
-        oh[I] = gram_operand<LDR>(tile[2 * wave], kk, I, lane);
-        ol[I] = gram_operand<LDR>(tile[2 * wave + 1], kk, I, lane);
+        oh[I] = gram_operand<D>(tile[2 * wave], kk, operand_at<D>(I, lane));
+        ol[I] = gram_operand<D>(tile[2 * wave + 1], kk, operand_at<D>(I, lane));
       }
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
@@ -589,7 +619,7 @@ __global__ __launch_bounds__(512) void probe_dgram4_kernel(ProbeParams P) {
   if (lane == 0) red[wave] = part;
   __syncthreads();
   if (tid < 2)
-    P.partial[((uint64_t)unit * P.n_chunks + chunk) * 2 + tid] = (red[tid] + red[2 + tid]) + (red[4 + tid] + red[6 + tid]);
+    P.partial[((uint64_t)unit * P.max_chunks + chunk) * 2 + tid] = (red[tid] + red[2 + tid]) + (red[4 + tid] + red[6 + tid]);
 }
 
 __global__ void probe_finalize_kernel(ProbeParams P) {
@@ -598,7 +628,8 @@ __global__ void probe_finalize_kernel(ProbeParams P) {
   if (i >= units * 2) return;
   const int unit = i >> 1, m = i & 1;
   double s = 0.0;
-  for (int c = 0; c < P.n_chunks; ++c) s += (double)P.partial[((uint64_t)unit * P.n_chunks + c) * 2 + m];
+  const int n = P.used_chunks[P.bsizes[unit / P.hkv] == 4];
+  for (int c = 0; c < n; ++c) s += (double)P.partial[((uint64_t)unit * P.max_chunks + c) * 2 + m];
   const int G = P.hq / P.hkv;
   const double nl = (double)P.bsizes[unit / P.hkv];
   P.errors[unit * 2 + m] = (float)(s / (nl * G * (double)P.n_probe * (double)P.d));

