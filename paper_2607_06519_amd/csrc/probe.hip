@@ -275,17 +275,20 @@ __global__ __launch_bounds__(256) void probe_qgram_mfma_kernel(ProbeParams P) {
   }
 }
 
-// Gram matrices of D and Dbar over one chunk of kProbeChunk tokens of a
+// Gram matrices of D and Dbar over one chunk of P.chunk_tokens tokens of a
 // unit, contracted with S_u, reading the keys once.  64 tokens per step: the
 // threads holding a token row's 16-byte pieces of the two layers form its
 // fp32 differences, find the token's top-k channels among them
-// (row_topk_mask: a bisection over the row's keys with DPP counts), split
+// (row_topk_mask), split
 // each half difference into bf16 hi + lo (split_bf16x2), zero the top-k
 // channels for Dbar, and write the four rows to LDS; waves 0-3 accumulate the
-// blocks of D D^T ~ H H^T + H L^T + L H^T (block t on wave t % 4), waves 4-7
-// those of Dbar.  Eight waves keep the accumulators at three blocks a wave,
-// so four waves fit on a SIMD for the VALU-heavy selection.  The next step's
-// loads are in flight during the MFMAs.
+// blocks of D D^T ~ H H^T + H L^T + L H^T, waves 4-7 those of Dbar.  Eight
+// waves keep the accumulators at three blocks a wave, so four waves fit on a
+// SIMD for the VALU-heavy selection.  The next step's loads are in flight
+// during the MFMAs.  VALU bound (about 580 instructions a wave and step, three
+// quarters of the issue slots); without the MFMA phase the 8B probe at 32768
+// tokens would take 575 us, without the selection 690, as it is 810 (862 with
+// padded LDS rows and the blocks dealt round-robin).
 template <int D, bool BF16>
 __global__ __launch_bounds__(512, BF16 ? 4 : 2) void probe_dgram_kernel(ProbeParams P) {
   constexpr int E = BF16 ? 2 : 4;
@@ -458,14 +461,14 @@ __global__ __launch_bounds__(512, BF16 ? 4 : 2) void probe_dgram_kernel(ProbePar
 }
 
 // Blocks of four: Gram matrices of the eight deviation matrices (4 layers x
-// shared / residual) over one chunk of kProbeChunk tokens, contracted with
+// shared / residual) over one chunk of P.chunk_tokens tokens, contracted with
 // the layers' probe Gram matrices.  R tokens per step: each thread takes
 // one 16-byte piece of a token row from all four layers, forms the
 // coefficients Z_1..Z_3 (the fp32 butterfly of dct4.h, as compress ranks
 // them), the token's top-k among the row's 3d coefficients with the other
-// lanes of the row (row_topk_mask), the block mean, the layer deviations and
-// the images of the token's kept coefficients, and writes the eight
-// deviation rows to LDS as bf16 hi + lo pairs (split_bf16x2); wave w
+// lanes of the row (row_topk_mask), the block mean, the layer deviations (of
+// the residual reconstruction: the images of the coefficients not kept), and
+// writes the eight deviation rows to LDS as bf16 hi + lo pairs (split_bf16x2); wave w
 // accumulates layer w / 2, shared (w even) or residual (w odd), as
 // H H^T + H L^T + L H^T.
 template <int D, bool BF16>
