@@ -142,7 +142,7 @@ def kernel_source_hash(read=None):
             with open(os.path.join(ROOT, "paper_2607_06519_amd", "csrc", name)) as f:
                 return f.read()
     h = hashlib.sha256()
-    for name in ("decode.hip", "decode_stream.hip", "decode_stream.h", "fdkv_common.h", "fdkv_kernels.h"):
+    for name in ("decode.hip", "decode_stream.hip", "decode_stream.h", "decode_shape.h", "fdkv_common.h", "fdkv_kernels.h"):
         h.update(code_tokens(read(name)).encode())
     return h.hexdigest()[:16]
 

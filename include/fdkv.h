@@ -265,9 +265,9 @@ fdkv_status fdkv_decode_workspace(const fdkv_dims* dims, int32_t batch, int32_t 
  *   sm_scale     logit scale (the paper uses 1/sqrt(d))
  *   ws           device workspace of >= fdkv_decode_workspace() bytes; with four
  *                times that (two times at Hq / Hkv = 8) a call of few chunks of
- *                512 tokens (at most 192 over all sequences and KV heads, bf16
- *                or FP8 cache) runs its chunks on several workgroups each, with
- *                the same results in about half the time
+ *                512 tokens (at most 192 over all sequences and KV heads) runs
+ *                its chunks on several workgroups each, with the same results
+ *                in about half the time
  */
 fdkv_status fdkv_decode_attn(const fdkv_dims* dims, int32_t batch, const int32_t* seq_lens,
                              int32_t max_seq_len, const uint8_t* modes, const uint64_t* seg_offsets,

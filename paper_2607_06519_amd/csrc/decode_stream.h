@@ -8,7 +8,7 @@
 // take the workgroup's tiles in turn (tile t of wave w: tile 4t + w), so at any
 // time they read one short run of each plane; the rows of a token-level set are
 // taken afterwards by the wave whose consecutive tokens hold them.  A call of
-// few chunks splits each over groups of four waves instead (Shape, below).
+// few chunks splits each over groups of four waves instead (decode_shape.h).
 //
 // One lane layout serves the K pass, the softmax and the V pass: NP = d/8
 // lanes per token row, each holding one 16-byte piece (8 channels), so one
@@ -53,6 +53,7 @@
 // workgroup per chunk, 9.4 us with groups; 32768 tokens 31.3 -> 29.1 us.
 #pragma once
 
+#include "decode_shape.h"
 #include "fdkv_common.h"
 #include "fdkv_kernels.h"
 
@@ -228,15 +229,6 @@ __device__ __forceinline__ void row_gather(uint32_t x, uint32_t (&y)[G], int lan
   if constexpr (G >= 8) gather_stage<SH + 2, 4>(y, lane);
 }
 
-// Launch shapes of a chunk of 512 tokens (one split-K record).
-//  kFull   - one workgroup of 4 waves, 128 tokens a wave.
-//  kWide   - one workgroup of 4 NGRP waves; a group of 4 waves takes
-//            512 / NGRP consecutive tokens.
-//  kSpread - the groups of kWide as NGRP workgroups, each writing a record of
-//            its own, which the merge folds into the chunk's record with
-//            kWide's arithmetic (the two give the same bits).
-enum Shape : int { kFull, kWide, kSpread };
-
 template <int D, int G, int SHAPE>
 struct SS {
   static constexpr int NP = D / 8;                 // lanes per row, one 16-byte piece each
@@ -281,24 +273,12 @@ struct TileBuf {
 
 }  // namespace
 
-// The unit arrays as constant memory, so that uniform reads are scalar loads
-// (the kernel does not write them).
-template <class X>
-__device__ __forceinline__ const __attribute__((address_space(4))) X* as_const(const X* p) {
-  return (const __attribute__((address_space(4))) X*)p;
-}
-
 // Bit h of the result: byte h of four mode bytes says residual (whatever its fraction).
 __device__ __forceinline__ uint32_t residual_bytes(uint32_t m) {
   uint32_t r = 0;
 #pragma unroll
   for (int h = 0; h < 4; ++h) r |= ((m >> (8 * h)) & 0xE3u) == (uint32_t)kResidual ? 1u << h : 0u;
   return r;
-}
-
-// Weight of a partial sum with reference max m in a sum with reference max M.
-__device__ __forceinline__ float merge_weight(float m, float M) {
-  return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
 }
 
 // MULTI: the call has several parts (spans and the exact tail); otherwise

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams P) {
   }
 }
 
-// The launch shapes and their rule: decode_stream.h, kDecodeSmallChunks.
+// The launch shapes: decode_shape.h; their rule: kDecodeSmallChunks.
 hipError_t launch_decode_stream(const DecodeParams& P, hipStream_t s) {
   if (P.n_chunks_total <= 0) return hipSuccess;
   if (P.d == 128) {
@@ -156,11 +156,10 @@ hipError_t launch_decode_stream(const DecodeParams& P, hipStream_t s) {
 template <int D, bool BF16, int G>
 static hipError_t launch_merge_g(const DecodeParams& P, hipStream_t s) {
   const dim3 grid((unsigned)P.batch * P.hq);
-  if (P.n_sub > 1) {
-    if constexpr (BF16) hipLaunchKernelGGL((decode_merge_kernel<D, BF16, G, decode_groups(G)>), grid, dim3(256), 0, s, P);
-  } else {
+  if (P.n_sub > 1)
+    hipLaunchKernelGGL((decode_merge_kernel<D, BF16, G, decode_groups(G)>), grid, dim3(256), 0, s, P);
+  else
     hipLaunchKernelGGL((decode_merge_kernel<D, BF16, G, 1>), grid, dim3(256), 0, s, P);
-  }
   return hipGetLastError();
 }
 

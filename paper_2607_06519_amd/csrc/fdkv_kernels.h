@@ -80,12 +80,12 @@ __host__ __device__ __forceinline__ int unit_ppm(int res_ppm, int n_rates, const
 constexpr int kDecodeChunk = 128;
 constexpr int kDecodeWaves = 4;
 constexpr int kDecodeWgTokens = kDecodeChunk * kDecodeWaves;
-// Groups of four waves that share a chunk of a small call (decode_stream.h):
+// Groups of four waves that share a chunk of a small call (decode_shape.h):
 // 128 tokens a group, or 256 with eight query heads, where the accumulators of
 // sixteen waves would pass the LDS of a workgroup.
 __host__ __device__ constexpr int decode_groups(int G) { return G == 8 ? 2 : 4; }
-// A bf16 or FP8 decode call of at most this many chunks over all (sequence, KV
-// head) pairs is small: its chunks are split over groups of waves.  One
+// A decode call of at most this many chunks over all (sequence, KV head) pairs
+// is small: its chunks are split over groups of waves.  One
 // workgroup per chunk then leaves at least a quarter of the 256 CUs idle, and
 // each of the others is bound by what one CU can keep in flight (a chunk of
 // 512 tokens is 262 KB).  Per layer on the 8B shape (8 KV heads, one sequence),
@@ -121,7 +121,7 @@ struct DecodeParams {
   bool tokres;                 // residual heads hold a token-level residual set
   bool bf16;
   bool coef8;                  // shared planes and residual values of shared / residual heads in FP8 E4M3
-  bool wide;                   // a chunk's groups of waves in one workgroup (decode_stream.h, kWide)
+  bool wide;                   // a chunk's groups of waves in one workgroup (decode_shape.h, kWide)
   int n_rates;                 // routed fractions of the sets (0: every set keeps res_ppm)
   int res_ppm, tail_part;
   // Parts of one call: compressed spans, then (if tail_part >= 0) the exact
