@@ -256,9 +256,9 @@ __device__ __forceinline__ void residual_entries4(const uint4 (&x)[4], int k, in
 
 // Waves per SIMD: four for pairs (128 VGPRs with K and V taken in turn),
 // three for blocks of four.  Left to itself the compiler gives blocks of
-// four with bf16 inputs 180 VGPRs (two waves); held to 168 they spill three
-// and the mixed 8B prefill compress takes 2.15 instead of 2.68 ms (held to
-// 128 they spill 31 and take 2.58 ms).
+// four with bf16 inputs more than 168 VGPRs (two waves); held to 168 they spill
+// two, held to 128 they spill 42 and 16 layers of the 8B shape, nearly all
+// residual, take 1236 in place of 808 us.
 template <int D, bool BF16, int NB>
 __global__ __launch_bounds__(256, NB == 2 ? 4 : 3) void compress_dense_kernel(CompressParams P) {
   using Ly = DenseLayout<D, BF16, NB>;
@@ -299,6 +299,69 @@ __global__ __launch_bounds__(256, NB == 2 ? 4 : 3) void compress_dense_kernel(Co
   const bool pad8 = c8 && mode != kExact;
   const int t_end = pad8 ? (T + R8 - 1) / R8 * R8 : T;
   static_assert(RPP % R8 == 0 || !BF16, "FP8 blocks within a pass");
+  if constexpr (NB == 4) {
+    // Blocks of four: K and V of a row are taken in turn, and a tensor's next
+    // rows load while the other's are ranked and written.  (Residual heads rank
+    // 3 CPP coefficients a lane; with both tensors' rows loaded at the start of
+    // every pass, three waves to a SIMD hid little of the wait.  16 layers of
+    // the 8B shape at 32768 tokens, nearly all heads residual: 934 -> 808 us,
+    // 3.6 TB/s; half of the heads shared: 735 -> 648 us.)
+    static_assert(PPT == 1, "one piece a thread");
+    const int wave = threadIdx.x >> 6, rw = (threadIdx.x & 63) / LPR;
+    uint4 ka[NB], va[NB];
+    auto load_rows = [&](const uint8_t* const* x, int t, uint4 (&a)[NB]) {
+      const uint64_t off = (uint64_t)t * row_bytes + lr * 16;
+#pragma unroll
+      for (int n = 0; n < NB; ++n) a[n] = t < T ? load_stream(x[n] + off) : make_uint4(0u, 0u, 0u, 0u);
+    };
+    auto store_row = [&](int t, const uint4 (&a)[NB], const uint64_t mplane, const uint64_t* eplane) {
+      const uint64_t off = (uint64_t)t * row_bytes + lr * 16;
+      if (t >= T) {
+        if (pad8 && t < t_end)
+          *reinterpret_cast<uint2*>(seg + mplane + c8_piece_offset((uint64_t)t, lr, D)) = make_uint2(0u, 0u);
+      } else if (mode == kExact) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) store_stream(seg + eplane[n] + off, a[n]);
+      } else if (c8) {
+        *reinterpret_cast<uint2*>(seg + mplane + c8_piece_offset((uint64_t)t, lr, D)) = mean_piece_e4m3<NB>(a);
+      } else {
+        store_stream(seg + mplane + off, mean_piece<BF16, NB>(a));
+      }
+    };
+    load_rows(kx, row0, ka);
+    load_rows(vx, row0, va);
+#pragma unroll 1
+    for (int r = 0; r < kCompressTile; r += RPP) {
+      const int t = row0 + r, t0w = blockIdx.x * kCompressTile + r + wave * RPW;
+      // rows past the end: the entries need every lane of a wave, so a
+      // workgroup with residual rows runs the pass to the end on zeros and
+      // stores nothing for them (but the FP8 block padding)
+      if (!resid && t >= t_end) break;
+      if (resid && (int)blockIdx.x * kCompressTile + r >= T) break;
+      const bool more = r + RPP < kCompressTile;
+      uint32_t kpre = 0;
+      if (resid && P.ksel && t < T)
+        kpre = *reinterpret_cast<const uint32_t*>(P.ksel + selection_offset(unit, T, t, lr, D, E, 4));
+      store_row(t, ka, L.mk, L.ek);
+      if (resid) {
+        const uint32_t* kp = P.ksel ? &kpre : nullptr;
+        if (c8)
+          residual_entries4<D, BF16, true>(ka, P.topk, rw, t0w, T, seg + L.ik, seg + L.vk, stage[wave], kp);
+        else
+          residual_entries4<D, BF16, false>(ka, P.topk, rw, t0w, T, seg + L.ik, seg + L.vk, stage[wave], kp);
+      }
+      if (more) load_rows(kx, t + RPP, ka);
+      store_row(t, va, L.mv, L.ev);
+      if (resid) {
+        if (c8)
+          residual_entries4<D, BF16, true>(va, P.topk, rw, t0w, T, seg + L.iv, seg + L.vv, stage[wave]);
+        else
+          residual_entries4<D, BF16, false>(va, P.topk, rw, t0w, T, seg + L.iv, seg + L.vv, stage[wave]);
+      }
+      if (more) load_rows(vx, t + RPP, va);
+    }
+    return;
+  }
 #pragma unroll 2
   for (int r = 0; r < kCompressTile; r += RPP) {
     const int t = row0 + r;
@@ -340,7 +403,6 @@ __global__ __launch_bounds__(256, NB == 2 ? 4 : 3) void compress_dense_kernel(Co
       }
     };
     static_assert(PPT <= 2, "pieces per thread");
-    static_assert(PPT == 1 || NB == 2, "blocks of four: one piece a thread");
     const int wave = threadIdx.x >> 6;
     const int t0w = blockIdx.x * kCompressTile + r + wave * RPW;
     const int rw = (threadIdx.x & 63) / LPR;
@@ -386,55 +448,6 @@ __global__ __launch_bounds__(256, NB == 2 ? 4 : 3) void compress_dense_kernel(Co
           residual_entries<D, BF16, true>(va, P.topk, rw, t0w, T, seg + L.iv, seg + L.vv, stage[wave]);
         else
           residual_entries<D, BF16, false>(va, P.topk, rw, t0w, T, seg + L.iv, seg + L.vv, stage[wave]);
-      }
-    } else {
-      // blocks of four: both tensors' rows in flight together, both planes'
-      // stores, then the entries (of the orders tried, the one that spills
-      // the fewest registers at three waves per SIMD)
-#pragma unroll
-      for (int h = 0; h < PPT; ++h) {
-        const uint64_t off = (uint64_t)t * row_bytes + (h * LPR + lr) * 16;
-#pragma unroll
-        for (int n = 0; n < NB; ++n) {
-          ka[h][n] = live ? load_stream(kx[n] + off) : make_uint4(0u, 0u, 0u, 0u);
-          va[h][n] = live ? load_stream(vx[n] + off) : make_uint4(0u, 0u, 0u, 0u);
-        }
-      }
-      {
-        const uint64_t off = (uint64_t)t * row_bytes + lr * 16;
-        if (!live) {
-          if (pad8 && t < t_end) {
-            const uint64_t o8 = c8_piece_offset((uint64_t)t, lr, D);
-            *reinterpret_cast<uint2*>(seg + L.mk + o8) = make_uint2(0u, 0u);
-            *reinterpret_cast<uint2*>(seg + L.mv + o8) = make_uint2(0u, 0u);
-          }
-        } else if (mode == kExact) {
-#pragma unroll
-          for (int n = 0; n < NB; ++n) {
-            store_stream(seg + L.ek[n] + off, ka[0][n]);
-            store_stream(seg + L.ev[n] + off, va[0][n]);
-          }
-        } else if (c8) {
-          const uint64_t o8 = c8_piece_offset((uint64_t)t, lr, D);
-          *reinterpret_cast<uint2*>(seg + L.mk + o8) = mean_piece_e4m3<NB>(ka[0]);
-          *reinterpret_cast<uint2*>(seg + L.mv + o8) = mean_piece_e4m3<NB>(va[0]);
-        } else {
-          store_stream(seg + L.mk + off, mean_piece<BF16, NB>(ka[0]));
-          store_stream(seg + L.mv + off, mean_piece<BF16, NB>(va[0]));
-        }
-      }
-      if (resid) {
-        uint32_t kpre = 0;
-        if (P.ksel && live)
-          kpre = *reinterpret_cast<const uint32_t*>(P.ksel + selection_offset(unit, T, t, lr, D, E, 4));
-        const uint32_t* kp = P.ksel ? &kpre : nullptr;
-        if (c8) {
-          residual_entries4<D, BF16, true>(ka[0], P.topk, rw, t0w, T, seg + L.ik, seg + L.vk, stage[wave], kp);
-          residual_entries4<D, BF16, true>(va[0], P.topk, rw, t0w, T, seg + L.iv, seg + L.vv, stage[wave]);
-        } else {
-          residual_entries4<D, BF16, false>(ka[0], P.topk, rw, t0w, T, seg + L.ik, seg + L.vk, stage[wave], kp);
-          residual_entries4<D, BF16, false>(va[0], P.topk, rw, t0w, T, seg + L.iv, seg + L.vv, stage[wave]);
-        }
       }
     }
   }
