@@ -95,19 +95,18 @@ __device__ __forceinline__ bf16x8_t pack8(const float (&v)[8]) {
 }  // namespace
 
 // ---------------------------------------------------------------- scores
-// Eight waves (512 tokens) per workgroup share each round of probe rows in
-// LDS: half the probe-row traffic of four waves, 2.35 -> 2.25 ms on the 8B
-// token-set probe (sixteen waves, or 64 rows a round, lose occupancy).
+// fp32 probe rows and keys: eight waves (512 tokens) per workgroup share each
+// round of 32 probe rows in LDS.
 constexpr int kScoreThreads = 512;
 
-template <int D, bool BF16, int NB>
+template <int D, int NB>
 __global__ __launch_bounds__(kScoreThreads) void token_score_kernel(TokenParams P) {
   constexpr int TH = kScoreThreads;
-  constexpr int E = BF16 ? 2 : 4;
+  constexpr int E = 4;
   constexpr int KS = D / 16;                 // k-steps of the 32x32x16 MFMA
   constexpr int NPQ = D / 8;                 // 8-channel pieces of a probe row
   constexpr int LDR = D + 8;                 // LDS row stride (bf16 elements): 16-byte pad
-  constexpr int NH = BF16 ? 1 : 2;           // bf16 halves of a query (fp32 queries: hi + lo)
+  constexpr int NH = 2;                      // bf16 halves of a query: hi + lo
   constexpr int NL = NB == 2 ? 1 : NB;       // deviation passes (a pair's two layers share one up to sign)
   __shared__ __attribute__((aligned(16))) uint16_t qs[NH][32 * LDR];
 
@@ -140,7 +139,7 @@ __global__ __launch_bounds__(kScoreThreads) void token_score_kernel(TokenParams 
         const uint32_t off = (uint32_t)t * (uint32_t)RB + (uint32_t)((2 * ks + kh) * 8 * E);
         float x[NB][8];
 #pragma unroll
-        for (int n = 0; n < NB; ++n) load8<BF16>(kr[n], off, ok, x[n]);
+        for (int n = 0; n < NB; ++n) load8<false>(kr[n], off, ok, x[n]);
         float dv[8];
 #pragma unroll
         for (int c = 0; c < 8; ++c) dv[c] = deviation<NB>(x, pass, c);
@@ -160,7 +159,7 @@ __global__ __launch_bounds__(kScoreThreads) void token_score_kernel(TokenParams 
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
           const int i = tid + TH * j, row = i / NPQ, pc = i % NPQ;
-          load8<BF16>(qr, (uint32_t)((r0 + row) * RB + pc * 8 * E), i < 32 * NPQ && r0 + row < GP, qn[j]);
+          load8<false>(qr, (uint32_t)((r0 + row) * RB + pc * 8 * E), i < 32 * NPQ && r0 + row < GP, qn[j]);
         }
       };
       fetch(0);
@@ -175,12 +174,10 @@ __global__ __launch_bounds__(kScoreThreads) void token_score_kernel(TokenParams 
 #pragma unroll
           for (int jj = 0; jj < 4; ++jj) {
             hi[jj] = pack_bf16x2(q[2 * jj], q[2 * jj + 1]);
-            if constexpr (NH == 2)
-              lo[jj] = pack_bf16x2(q[2 * jj] - bf16_lo(hi[jj]), q[2 * jj + 1] - bf16_hi(hi[jj]));
+            lo[jj] = pack_bf16x2(q[2 * jj] - bf16_lo(hi[jj]), q[2 * jj + 1] - bf16_hi(hi[jj]));
           }
           *reinterpret_cast<uint4*>(&qs[0][row * LDR + pc * 8]) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-          if constexpr (NH == 2)
-            *reinterpret_cast<uint4*>(&qs[NH - 1][row * LDR + pc * 8]) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+          *reinterpret_cast<uint4*>(&qs[1][row * LDR + pc * 8]) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
         }
         __syncthreads();
         if (r0 + 32 < GP) fetch(r0 + 32);
@@ -209,6 +206,165 @@ __global__ __launch_bounds__(kScoreThreads) void token_score_kernel(TokenParams 
             ss[st] = fmaf(v, v, ss[st]);
           }
       }
+    }
+  }
+  // lanes l and l + 32 saw the other 16 rows of each block for the same token
+#pragma unroll
+  for (int st = 0; st < 2; ++st) {
+    mx[st] = fmaxf(mx[st], __shfl_xor(mx[st], 32, 64));
+    ss[st] += __shfl_xor(ss[st], 32, 64);
+  }
+  if (kh == 0) {
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const int t = tok_w + st * 32 + tl;
+      if (t < T) {
+        P.scores[(uint64_t)unit * T + t] = mx[st];
+        if (P.sumsq) P.sumsq[(uint64_t)unit * T + t] = ss[st];
+      }
+    }
+  }
+}
+
+// bf16 probe rows and keys: the same products, arranged so that the matrix cores
+// wait less.  64 rows of probe a round in one of two LDS tiles (the next
+// round's rows are in registers and go to the other tile, so a round has one
+// barrier), and the max and square of one block of 32 rows are taken between
+// the MFMAs of the next (three VALU instructions to an MFMA).  Rows are
+// unpadded, 16-byte pieces permuted by the row so that 16 lanes of a read touch
+// every bank once.  At d = 128 four waves a workgroup, two workgroups to a CU:
+// one builds its deviations while the other multiplies (eight waves in one
+// workgroup took 5% longer, 25% with blocks of four).  Bound by MFMA and VALU
+// issue together (51% and 35% of the cycles at eight waves).  Probe of 16 layers
+// of the 8B shape against one 32-row tile with a barrier on each side: 32768
+// tokens 1042 -> 994 us (pairs), 2450 -> 1734 (blocks of four), 648 -> 543 at
+// d = 64; 500 tokens 92 -> 51.
+constexpr int score_threads(int d) { return d == 128 ? 256 : 512; }
+
+template <int D, int NB>
+__global__ __launch_bounds__(score_threads(D), 2) void token_score_bf16_kernel(TokenParams P) {
+  constexpr int TH = score_threads(D);
+  constexpr int KS = D / 16;                 // k-steps of the 32x32x16 MFMA
+  constexpr int NPQ = D / 8;                 // 16-byte pieces of a row
+  constexpr int R = 64, PER = R * NPQ / TH;  // probe rows a round, pieces per thread and round
+  constexpr int NL = NB == 2 ? 1 : NB;       // deviation passes (a pair's two layers share one up to sign)
+  static_assert(PER >= 1, "shape");
+  __shared__ __attribute__((aligned(16))) uint16_t qs[2][R * D];
+
+  const int bi = blockIdx.y / P.hkv, head = blockIdx.y % P.hkv;
+  const int first = P.bl.first[bi];
+  const int unit = P.bl.block[bi] * P.hkv + head;
+  const int T = P.seq_len, G = P.hq / P.hkv, GP = G * P.n_probe;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  constexpr uint32_t RB = D * 2;
+  const uint64_t plane = (uint64_t)T * RB;
+  __amdgpu_buffer_rsrc_t kr[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+    kr[n] = make_rsrc(static_cast<const uint8_t*>(P.k[first + n]) + (uint64_t)head * plane, plane);
+  const uint64_t qspan = (uint64_t)GP * RB;  // one layer's probe rows of this KV head
+
+  const int tl = lane & 31, kh = lane >> 5;
+  const int tok_w = blockIdx.x * TH + wave * 64;   // the wave's 64 tokens: two sets of 32
+  float mx[2] = {0.f, 0.f}, ss[2] = {0.f, 0.f};
+
+  for (int pass = 0; pass < NL; ++pass) {
+    // B operands: the deviation rows of the wave's tokens for this pass
+    bf16x8_t bop[2][KS];
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const int t = tok_w + st * 32 + tl;
+      const bool ok = t < T;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const uint32_t off = (uint32_t)t * RB + (uint32_t)((2 * ks + kh) * 16);
+        float x[NB][8];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) load8<true>(kr[n], off, ok, x[n]);
+        float dv[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) dv[c] = deviation<NB>(x, pass, c);
+        bop[st][ks] = pack8(dv);
+        if (NB == 4 && ks % 2) __builtin_amdgcn_sched_barrier(0);  // two pieces of all layers in flight: registers
+      }
+    }
+    const int nlay = NB == 2 ? 2 : 1;
+    for (int ly = 0; ly < nlay; ++ly) {
+      const int layer = first + (NB == 2 ? ly : pass);
+      const auto qr = make_rsrc(static_cast<const uint8_t*>(P.qp[layer]) + (uint64_t)head * qspan, qspan);
+      const int rounds = (GP + R - 1) / R;
+      uint4 next[PER];
+      auto fetch = [&](int r) {  // rows past the last read zeros: logits of 0
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+          const int i = tid + TH * j, row = r * R + i / NPQ;
+          next[j] = load16(qr, row < GP ? (uint32_t)row * RB + (uint32_t)(i % NPQ) * 16 : kOobOff);
+        }
+      };
+      auto swz = [](int row) { return D == 128 ? row & 15 : (row >> 1) & 7; };
+      auto stage = [&](int b) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+          const int i = tid + TH * j, row = i / NPQ, pc = i % NPQ;
+          *reinterpret_cast<uint4*>(&qs[b][row * D + (pc ^ swz(row)) * 8]) = next[j];
+        }
+      };
+      // the 32 rows of a block against the wave's tokens
+      auto block = [&](const uint16_t* tile, f32x16_t (&acc)[2]) {
+        const f32x16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const bf16x8_t aop =
+              *reinterpret_cast<const bf16x8_t*>(&tile[tl * D + ((2 * ks + kh) ^ swz(tl)) * 8]);
+#pragma unroll
+          for (int st = 0; st < 2; ++st)
+            acc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aop, bop[st][ks], ks ? acc[st] : zero, 0, 0, 0);
+        }
+      };
+      // lane holds 16 rows of its token (column tl)
+      auto take = [&](const f32x16_t (&acc)[2]) {
+#pragma unroll
+        for (int r = 0; r < 16; r += 2)
+#pragma unroll
+          for (int st = 0; st < 2; ++st) {
+            const float v = acc[st][r], w = acc[st][r + 1];
+            mx[st] = fmaxf(fmaxf(mx[st], fabsf(v)), fabsf(w));
+            ss[st] = fmaf(v, v, ss[st]);
+            ss[st] = fmaf(w, w, ss[st]);
+          }
+      };
+      auto interleave = [&]() {  // one MFMA, then three VALU instructions
+#pragma unroll
+        for (int i = 0; i < 2 * KS; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 48 / (2 * KS), 0);
+        }
+      };
+      fetch(0);
+      __syncthreads();  // the tiles' readers of the layer before are done
+      stage(0);
+      if (rounds > 1) fetch(1);
+      __syncthreads();
+      f32x16_t a0[2], a1[2];
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) a1[st][r] = 0.f;  // of no rows yet
+      for (int r = 0; r < rounds; ++r) {
+        const uint16_t* tile = qs[r & 1];
+        if (r + 1 < rounds) {
+          stage((r + 1) & 1);
+          if (r + 2 < rounds) fetch(r + 2);
+        }
+        block(tile, a0);
+        take(a1);
+        interleave();
+        block(tile + 32 * D, a1);
+        take(a0);
+        interleave();
+        __syncthreads();
+      }
+      take(a1);
     }
   }
   // lanes l and l + 32 saw the other 16 rows of each block for the same token
@@ -513,8 +669,12 @@ __global__ __launch_bounds__(256) void token_rows_kernel(TokenParams P) {
 // ---------------------------------------------------------------- launchers
 template <int D, bool BF16, int NB>
 static hipError_t launch_scores_t(const TokenParams& P, hipStream_t s) {
-  const dim3 grid((P.seq_len + kScoreThreads - 1) / kScoreThreads, P.bl.n * P.hkv);
-  hipLaunchKernelGGL((token_score_kernel<D, BF16, NB>), grid, dim3(kScoreThreads), 0, s, P);
+  constexpr int th = BF16 ? score_threads(D) : kScoreThreads;
+  const dim3 grid((P.seq_len + th - 1) / th, P.bl.n * P.hkv);
+  if constexpr (BF16)
+    hipLaunchKernelGGL((token_score_bf16_kernel<D, NB>), grid, dim3(th), 0, s, P);
+  else
+    hipLaunchKernelGGL((token_score_kernel<D, NB>), grid, dim3(th), 0, s, P);
   return hipGetLastError();
 }
 
