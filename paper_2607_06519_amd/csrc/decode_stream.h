@@ -266,7 +266,7 @@ struct SS {
 template <int NL>
 struct TileBuf {
   uint4 k[NL], v[NL];
-  // residual entry of the lane in each of its rows (k = NP path): index byte and bf16 value
+  // the lane's first residual entry in each of its rows: index and value
   uint32_t ki[NL], kv[NL], vi[NL], vv[NL];
   uint32_t tm;  // token-level residual set: the tile's word of the token mask
 };
@@ -448,10 +448,15 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
   }
 
   // The tile loop is specialised per residual flavour (RES: 0 none, 1 one
-  // entry per lane (k = NP), 2 any other k, 3 a token-level set: the set's
-  // tokens are masked out of the tile loop and taken afterwards in a pass of
-  // their own, rebuilt in full) so that every load of a tile is
-  // issued unconditionally: a tile past the wave's range takes the
+  // entry per lane (k = NP), 2 fewer, 4 more (the first two of a lane travel
+  // ahead of their tile, others are loaded where they are used), 3 a
+  // token-level set: the set's tokens are masked out of the tile loop and
+  // taken afterwards in a pass of their own, rebuilt in full) so that every
+  // load of a tile is
+  // issued unconditionally (k other than NP with its entries loaded in turn where
+  // they were used took, per layer of the 8B shape at 32768 tokens, 45.5 us at
+  // k = 5 and 59.1 at k = 24, now 29.5 and 35.0; d = 64, k = 16 at 12345 tokens
+  // 27.8, now 16.0): a tile past the wave's range takes the
   // out-of-range offset and reads zeros without touching memory.  With no
   // load behind a branch the compiler can wait for exactly the tile it needs
   // and leave the later tiles' loads in flight.
@@ -460,7 +465,7 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
     constexpr bool C8 = decltype(c8_tag)::value;  // FP8 planes and residual values
     constexpr bool Q4 = decltype(q4_tag)::value;  // block of four: uint16 codes 4c + j
     // planes of the residual entries (bytes below 2^31), after the shared ones
-    constexpr bool ENT = RES == 1 || RES == 2;
+    constexpr bool ENT = RES == 1 || RES == 2 || RES == 4;
     const uint32_t ibytes = ENT ? (uint32_t)T * k * (Q4 ? 2 : 1) : 0, vbytes = ENT ? (uint32_t)T * k * (C8 ? 1 : 2) : 0;
     const uint32_t iplane = (ibytes + kPlaneAlign - 1) / kPlaneAlign * kPlaneAlign;
     const uint32_t vplane = (vbytes + kPlaneAlign - 1) / kPlaneAlign * kPlaneAlign;
@@ -495,6 +500,8 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
     };
 
     constexpr int PD = (RES == 0 || RES == 3) ? S::PD0 : S::PD1, NB = PD + 1;
+    // the lane's first and second entry of a row, past k: the out-of-range offset
+    const uint32_t past0 = pc < k ? 0u : kOob, past1 = NP + pc < k ? 0u : kOob;
     // the wave's tile t: rows from row0(t), nt of them in the sequence
     // (interleaved over the waves: 1.1% off the 8B decode step against a
     // contiguous 128 tokens a wave)
@@ -523,12 +530,12 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
       for (int i = 0; i < NL; ++i) {
         const uint32_t row = r0 + i * RPL + rg;
         if constexpr (!C8) b.k[i] = ld128_stream(kr, (row * RB + pc * 16) | out);
-        if constexpr (RES == 1) {
-          const uint32_t e = row * NP + pc;
-          b.ki[i] = Q4 ? __builtin_amdgcn_raw_buffer_load_b16(ikr, (e * 2) | out, 0, kNonTemporal)
-                       : __builtin_amdgcn_raw_buffer_load_b8(ikr, e | out, 0, kNonTemporal);
-          b.kv[i] = C8 ? __builtin_amdgcn_raw_buffer_load_b8(vkr, e | out, 0, kNonTemporal)
-                       : __builtin_amdgcn_raw_buffer_load_b16(vkr, (e * 2) | out, 0, kNonTemporal);
+        if constexpr (ENT) {
+          const uint32_t e = RES == 1 ? row * NP + pc : row * k + pc, off = RES == 1 ? out : out | past0;
+          b.ki[i] = Q4 ? __builtin_amdgcn_raw_buffer_load_b16(ikr, (e * 2) | off, 0, kNonTemporal)
+                       : __builtin_amdgcn_raw_buffer_load_b8(ikr, e | off, 0, kNonTemporal);
+          b.kv[i] = C8 ? __builtin_amdgcn_raw_buffer_load_b8(vkr, e | off, 0, kNonTemporal)
+                       : __builtin_amdgcn_raw_buffer_load_b16(vkr, (e * 2) | off, 0, kNonTemporal);
         }
       }
       if constexpr (C8) {
@@ -540,13 +547,33 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
       for (int i = 0; i < NL; ++i) {
         const uint32_t row = r0 + i * RPL + rg;
         if constexpr (!C8) b.v[i] = ld128_stream(vr, (row * RB + pc * 16) | out);
-        if constexpr (RES == 1) {
-          const uint32_t e = row * NP + pc;
-          b.vi[i] = Q4 ? __builtin_amdgcn_raw_buffer_load_b16(ivr, (e * 2) | out, 0, kNonTemporal)
-                       : __builtin_amdgcn_raw_buffer_load_b8(ivr, e | out, 0, kNonTemporal);
-          b.vv[i] = C8 ? __builtin_amdgcn_raw_buffer_load_b8(vvr, e | out, 0, kNonTemporal)
-                       : __builtin_amdgcn_raw_buffer_load_b16(vvr, (e * 2) | out, 0, kNonTemporal);
+        if constexpr (ENT) {
+          const uint32_t e = RES == 1 ? row * NP + pc : row * k + pc, off = RES == 1 ? out : out | past0;
+          b.vi[i] = Q4 ? __builtin_amdgcn_raw_buffer_load_b16(ivr, (e * 2) | off, 0, kNonTemporal)
+                       : __builtin_amdgcn_raw_buffer_load_b8(ivr, e | off, 0, kNonTemporal);
+          b.vv[i] = C8 ? __builtin_amdgcn_raw_buffer_load_b8(vvr, e | off, 0, kNonTemporal)
+                       : __builtin_amdgcn_raw_buffer_load_b16(vvr, (e * 2) | off, 0, kNonTemporal);
         }
+      }
+    };
+
+    // RES 4: the lane's second entries of one tile, loaded for the next tile as
+    // soon as this one's are used (one set: two would cost the other flavours a
+    // wave per SIMD; none with eight query heads, which have no registers left)
+    constexpr bool X2 = RES == 4 && G < 8;
+    const int rest = X2 ? 2 * NP : NP;  // first entry that is loaded where it is used
+    uint32_t xki[NL], xkv[NL], xvi[NL], xvv[NL];
+    auto second = [&](int t, auto v_tag, uint32_t (&ix)[NL], uint32_t (&val)[NL]) {
+      constexpr bool V = decltype(v_tag)::value;
+      uint32_t out = t < nt ? 0u : kOob;
+      asm("" : "+s"(out));
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const uint32_t e = (uint32_t)(row0(t) + i * RPL + rg) * k + NP + pc, off = out | past1;
+        ix[i] = Q4 ? __builtin_amdgcn_raw_buffer_load_b16(V ? ivr : ikr, (e * 2) | off, 0, kNonTemporal)
+                   : __builtin_amdgcn_raw_buffer_load_b8(V ? ivr : ikr, e | off, 0, kNonTemporal);
+        val[i] = C8 ? __builtin_amdgcn_raw_buffer_load_b8(V ? vvr : vkr, e | off, 0, kNonTemporal)
+                    : __builtin_amdgcn_raw_buffer_load_b16(V ? vvr : vkr, (e * 2) | off, 0, kNonTemporal);
       }
     };
 
@@ -563,31 +590,32 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
           for (int w = 0; w < 4; ++w) a = dot2(word(kp, w), word(qreg[g], w), a);
           s[i][g] = a;
         }
-      if constexpr (RES == 1) {
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
+      if constexpr (ENT) {
+        auto add = [&](int i, uint32_t ix, uint32_t raw) {
           float w;
-          const int c = entry(b.ki[i], w);
-          const float v = w * bf16_to_f32((uint16_t)(C8 ? e4m3x2_bf16<false>(b.kv[i]) : b.kv[i]));
+          const int c = entry(ix, w);
+          const float v = w * bf16_to_f32((uint16_t)(C8 ? e4m3x2_bf16<false>(raw) : raw));
 #pragma unroll
           for (int g = 0; g < G; ++g) s[i][g] = fmaf(q_lds[c * G + g], v, s[i][g]);
-        }
-      } else if constexpr (RES == 2) {
+        };
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-          const uint32_t rc = (uint32_t)min(r0 + i * RPL + rg, T - 1);
-          for (int e = pc; e < k; e += NP) {
-            const uint32_t x = rc * k + e;
-            float w;
-            const int c = entry(Q4 ? __builtin_amdgcn_raw_buffer_load_b16(ikr, x * 2, 0, 0)
-                                   : __builtin_amdgcn_raw_buffer_load_b8(ikr, x, 0, 0), w);
-            const uint32_t raw = C8 ? e4m3x2_bf16<false>(__builtin_amdgcn_raw_buffer_load_b8(vkr, x, 0, 0))
-                                    : __builtin_amdgcn_raw_buffer_load_b16(vkr, x * 2, 0, 0);
-            const float v = w * bf16_to_f32((uint16_t)raw);
-#pragma unroll
-            for (int g = 0; g < G; ++g) s[i][g] = fmaf(q_lds[c * G + g], v, s[i][g]);
+          if (RES != 2 || pc < k) add(i, b.ki[i], b.kv[i]);
+          if constexpr (RES == 4) {
+            if (X2 && NP + pc < k) add(i, xki[i], xkv[i]);
+            const uint32_t rc = (uint32_t)min(r0 + i * RPL + rg, T - 1);
+            for (int e0 = rest; e0 < k; e0 += NP) {
+              const int e = e0 + pc;
+              const uint32_t x = e < k ? rc * k + e : kOob, x2 = e < k ? 2 * (rc * k + e) : kOob;
+              const uint32_t ix = Q4 ? __builtin_amdgcn_raw_buffer_load_b16(ikr, x2, 0, 0)
+                                     : __builtin_amdgcn_raw_buffer_load_b8(ikr, x, 0, 0);
+              const uint32_t raw = C8 ? __builtin_amdgcn_raw_buffer_load_b8(vkr, x, 0, 0)
+                                      : __builtin_amdgcn_raw_buffer_load_b16(vkr, x2, 0, 0);
+              if (e < k) add(i, ix, raw);
+            }
           }
         }
+        if constexpr (X2) second(t + 1, std::false_type{}, xki, xkv);
       }
       // probabilities of the lane's two rows per head as bf16 pairs (row 0
       // low), and as fp32 for the residual V entries
@@ -621,7 +649,7 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
             const float alpha = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(al), g << S::SH));
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc[g][c] *= alpha;
-            if constexpr (RES == 1 || RES == 2) {
+            if constexpr (ENT) {
 #pragma unroll
               for (int cp = 0; cp < RPL; ++cp)
 #pragma unroll
@@ -636,7 +664,7 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
         ls += pv;
         const float pq = swap_half<NP>(pv);  // the same head's other row
         row_gather<S::SH>(s_row == 0 ? cvt_bf16x2(pv, pq) : cvt_bf16x2(pq, pv), pp, lane);
-        if constexpr (RES == 1 || RES == 2) {
+        if constexpr (ENT) {
 #pragma unroll
           for (int g = 0; g < G; ++g) {
             p[0][g] = bf16_lo(pp[g]);
@@ -668,7 +696,7 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
             l[g] *= alpha;
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc[g][c] *= alpha;
-            if constexpr (RES == 1 || RES == 2) {
+            if constexpr (ENT) {
 #pragma unroll
               for (int cp = 0; cp < RPL; ++cp)
 #pragma unroll
@@ -709,45 +737,38 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
       // residual V entries: the lanes of one row hold distinct channels and
       // each row of a load has its own accumulator copy, so a plain
       // read-add-write never collides (masked rows add p = 0)
-      if constexpr (RES == 1) {
+      // (the lanes of a row take its entries NP at a time, all lanes in every
+      // step: entries past k read nothing and write nothing)
+      if constexpr (ENT) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-          float w;
-          const int c = entry(b.vi[i], w);
-          float v = w * bf16_to_f32((uint16_t)(C8 ? e4m3x2_bf16<false>(b.vv[i]) : b.vv[i]));
-          bool first = true;
-          if constexpr (Q4) v = run_sum<NP>(c, v, pc, true, true, true, first);
-          if (first) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) sp(wave, rg, g, c) += p[i][g] * v;
-          }
-        }
-      } else if constexpr (RES == 2) {
-        // the lanes of a row walk the row's entries NP at a time, all lanes
-        // in every step (entries past k read nothing and write nothing)
-        const int steps = (k + NP - 1) / NP;
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-          const int row = r0 + i * RPL + rg;
-          const uint32_t rc = (uint32_t)min(row, T - 1);
-          for (int st = 0; st < steps; ++st) {
-            const int e = st * NP + pc;
-            const bool valid = e < k;
-            const uint32_t x = rc * k + e;
+          auto step = [&](int e, uint32_t ix, uint32_t raw) {
             float w;
-            const int c = entry(Q4 ? __builtin_amdgcn_raw_buffer_load_b16(ivr, valid ? x * 2 : kOob, 0, 0)
-                                   : __builtin_amdgcn_raw_buffer_load_b8(ivr, valid ? x : kOob, 0, 0), w);
-            const uint32_t raw = C8 ? e4m3x2_bf16<false>(__builtin_amdgcn_raw_buffer_load_b8(vvr, valid ? x : kOob, 0, 0))
-                                    : __builtin_amdgcn_raw_buffer_load_b16(vvr, valid ? x * 2 : kOob, 0, 0);
-            float v = w * bf16_to_f32((uint16_t)raw);
-            bool first = valid;
-            if constexpr (Q4) v = run_sum<NP>(c, v, pc, valid, e + 1 < k, e + 2 < k, first);
+            const int c = entry(ix, w);
+            float v = w * bf16_to_f32((uint16_t)(C8 ? e4m3x2_bf16<false>(raw) : raw));
+            const bool all = RES == 1;
+            bool first = all || e < k;
+            if constexpr (Q4) v = run_sum<NP>(c, v, pc, all || e < k, all || e + 1 < k, all || e + 2 < k, first);
             if (first) {
 #pragma unroll
               for (int g = 0; g < G; ++g) sp(wave, rg, g, c) += p[i][g] * v;
             }
+          };
+          step(pc, b.vi[i], b.vv[i]);
+          if constexpr (RES == 4) {
+            if constexpr (X2) step(NP + pc, xvi[i], xvv[i]);
+            const uint32_t rc = (uint32_t)min(r0 + i * RPL + rg, T - 1);
+            for (int e0 = rest; e0 < k; e0 += NP) {
+              const int e = e0 + pc;
+              const uint32_t x = e < k ? rc * k + e : kOob, x2 = e < k ? 2 * (rc * k + e) : kOob;
+              const uint32_t ix = Q4 ? __builtin_amdgcn_raw_buffer_load_b16(ivr, x2, 0, 0)
+                                     : __builtin_amdgcn_raw_buffer_load_b8(ivr, x, 0, 0);
+              step(e, ix, C8 ? __builtin_amdgcn_raw_buffer_load_b8(vvr, x, 0, 0)
+                             : __builtin_amdgcn_raw_buffer_load_b16(vvr, x2, 0, 0));
+            }
           }
         }
+        if constexpr (X2) second(t + 1, std::true_type{}, xvi, xvv);
       }
     };
 
@@ -756,7 +777,11 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
     TileBuf<NL> buf[NB];
 #pragma unroll
     for (int i = 0; i < PD; ++i) load(i, buf[i]);
-    if constexpr (RES == 1 || RES == 2) {
+    if constexpr (X2) {
+      second(0, std::false_type{}, xki, xkv);
+      second(0, std::true_type{}, xvi, xvv);
+    }
+    if constexpr (ENT) {
       for (int x = lane * 4; x < RPL * G * D; x += 256)
         *reinterpret_cast<float4*>(&sp(wave, 0, 0, x)) = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
@@ -916,18 +941,23 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
   using R3 = std::integral_constant<int, 3>;
   using F = std::false_type;
   using Tr = std::true_type;
-  // residual heads: one entry per lane of a row (k = NP) or any other k, by block size
+  using R4 = std::integral_constant<int, 4>;
+  // residual heads: one entry per lane of a row (k = NP), fewer or more, by block size
   auto run_res = [&](auto c8_tag) {
     if (nb == 4) {
       if (k == NP)
         run(R1{}, c8_tag, Tr{});
-      else
+      else if (k < NP)
         run(R2{}, c8_tag, Tr{});
+      else
+        run(R4{}, c8_tag, Tr{});
     } else {
       if (k == NP)
         run(R1{}, c8_tag, F{});
-      else
+      else if (k < NP)
         run(R2{}, c8_tag, F{});
+      else
+        run(R4{}, c8_tag, F{});
     }
   };
   auto run_tok = [&](auto c8_tag) {
