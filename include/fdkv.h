@@ -241,7 +241,7 @@ fdkv_status fdkv_compress(const fdkv_dims* dims, int32_t seq_len, const void* co
                           const uint64_t* seg_offsets, const float* token_scores, const uint8_t* k_select,
                           void* cache, void* stream);
 
-/* Device workspace bytes fdkv_decode_attn needs for this batch shape. */
+/* Device workspace bytes for fdkv_decode_attn on this batch shape. */
 fdkv_status fdkv_decode_workspace(const fdkv_dims* dims, int32_t batch, int32_t max_seq_len, size_t* bytes);
 
 /*
@@ -263,11 +263,15 @@ fdkv_status fdkv_decode_workspace(const fdkv_dims* dims, int32_t batch, int32_t 
  *   q            device [batch][Hq][d]
  *   out          device [batch][Hq][d]
  *   sm_scale     logit scale (the paper uses 1/sqrt(d))
- *   ws           device workspace of >= fdkv_decode_workspace() bytes; with four
- *                times that (two times at Hq / Hkv = 8) a call of few chunks of
- *                512 tokens (at most 192 over all sequences and KV heads) runs
- *                its chunks on several workgroups each, with the same results
- *                in about half the time
+ *   ws           device workspace of fdkv_decode_workspace() bytes.  A call needs
+ *                batch x Hkv x max(ceil(max_seq_len / 512), 1) x Hq / Hkv x (d + 4) x 4
+ *                bytes (FDKV_E_WORKSPACE otherwise); the query's size for an fp32
+ *                cache holds more for short calls, which then run in less time.
+ *                A sequence's outputs are the same bits whatever the workspace,
+ *                the bound max_seq_len and the other sequences of the batch; of
+ *                an fp32 cache up to the rounding of fp32 sums, which are taken
+ *                in one order where batch x Hkv x ceil(max_seq_len / 512) <= 192
+ *                and in another above.
  */
 fdkv_status fdkv_decode_attn(const fdkv_dims* dims, int32_t batch, const int32_t* seq_lens,
                              int32_t max_seq_len, const uint8_t* modes, const uint64_t* seg_offsets,
@@ -376,7 +380,10 @@ fdkv_status fdkv_decode_spans_workspace(const fdkv_dims* dims, int32_t batch, in
  * sequence with no token in any part gets o = 0.  spans is a host array of
  * n_spans descriptors; the same limits as fdkv_decode_attn apply to each
  * span, and cap * d * elem_bytes < 2^31 to the tail.  The workspace's note at
- * fdkv_decode_attn applies, but for the last bits of the results.
+ * fdkv_decode_attn applies, with the chunks of all spans and of the tail's cap,
+ * but that a longer bound on one part moves the records of the parts after it and
+ * that the workspace of an fp32 cache counts too: both change the order of fp32
+ * sums.
  */
 fdkv_status fdkv_decode_spans(const fdkv_dims* dims, int32_t batch, int32_t n_spans, const fdkv_span* spans,
                               const fdkv_tail* tail, int32_t layer, const void* q, void* out, float sm_scale,

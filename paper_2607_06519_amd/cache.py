@@ -33,13 +33,6 @@ def to_device(x: np.ndarray, dtype: str, device="cuda"):
     return t.to(device=device).to(torch_dtype(dtype))
 
 
-def _workspace(need: int, device):
-    """Decode workspace: ``need`` bytes, or four times that up to 16 MiB, which lets a small call
-    run each chunk of tokens on several workgroups, with a record for each."""
-    torch = _torch()
-    return torch.empty(max(need, min(4 * need, 16 << 20)) // 4 + 64, dtype=torch.float32, device=device)
-
-
 class CompressedCache:
     """One compressed cache: ``batch`` sequences, modes ``[batch][n_blocks][Hkv]``."""
 
@@ -57,7 +50,8 @@ class CompressedCache:
         self.offsets = torch.from_numpy(self.offsets_host.astype(np.int64)).to(device)
         self.modes = torch.from_numpy(m).to(device)
         self.seq_lens = torch.tensor(self.seq_lens_host, dtype=torch.int32, device=device)
-        self.ws = _workspace(B.decode_workspace(dims, self.batch, self.max_seq_len), device)
+        self.ws = torch.empty(B.decode_workspace(dims, self.batch, self.max_seq_len) // 4 + 64,
+                              dtype=torch.float32, device=device)
 
     def compress(self, seq: int, k_layers, v_layers, stream=None, token_scores=None, k_select=None):
         """Write sequence ``seq`` from per-layer device tensors ``[Hkv][T][d]`` (``token_scores``
@@ -129,7 +123,7 @@ class Generation:
     def _refresh_ws(self):
         torch = _torch()
         n = B.decode_spans_workspace(self.dims, self.batch, [s.max_seq_len for s in self.spans], self.cap)
-        self._ws = _workspace(n, self.pos.device)
+        self._ws = torch.empty(n // 4 + 64, dtype=torch.float32, device=self.pos.device)
         self._span_desc = [B.Span(int(s.seq_lens.data_ptr()), s.max_seq_len, int(s.modes.data_ptr()),
                                   int(s.offsets.data_ptr()), int(s.buf.data_ptr())) for s in self.spans]
 

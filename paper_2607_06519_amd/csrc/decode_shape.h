@@ -7,13 +7,17 @@
 
 namespace fdkv {
 
-// Launch shapes of a chunk of 512 tokens (one split-K record).
+// Launch shapes of a chunk of 512 tokens (one split-K record) of an fp32 cache.
 //  kFull   - one workgroup of 4 waves, 128 tokens a wave.
 //  kWide   - one workgroup of 4 NGRP waves; a group of 4 waves takes
 //            512 / NGRP consecutive tokens.
 //  kSpread - the groups of kWide as NGRP workgroups, each writing a record of
 //            its own, which the merge folds into the chunk's record with
 //            kWide's arithmetic (the two give the same bits).
+// kFull and the other two differ by the rounding of fp32 sums.  bf16 and FP8
+// caches have the one shape of decode_stream.h: their probabilities are rounded
+// to bf16 against the reference max that a wave has reached, so another split of
+// a chunk would give outputs that differ by 2e-3 of their norm.
 enum Shape : int { kFull, kWide, kSpread };
 
 // The unit arrays as constant memory, so that uniform reads are scalar loads

@@ -1,14 +1,19 @@
 // Streaming split-K decode over a bf16 compressed cache (Section 3: the
 // reconstruction of Eq. 3 fused into the attention).
 //
-// A chunk is 512 tokens of one (sequence, KV head).  Where the chunks fill the
-// chip, one workgroup of 4 waves takes a chunk: a wave walks 128 tokens in
-// 8-row tiles (d = 128; 16 rows at d = 64) with an online softmax, keeping the
-// next tiles' loads in flight while it computes the current one.  The waves
-// take the workgroup's tiles in turn (tile t of wave w: tile 4t + w), so at any
-// time they read one short run of each plane; the rows of a token-level set are
-// taken afterwards by the wave whose consecutive tokens hold them.  A call of
-// few chunks splits each over groups of four waves instead (decode_shape.h).
+// A chunk is 512 tokens of one (sequence, KV head), taken by one workgroup of
+// 4 waves: a wave walks 128 tokens in 8-row tiles (d = 128; 16 rows at d = 64)
+// with an online softmax, keeping the next tiles' loads in flight while it
+// computes the current one.  The waves take the workgroup's tiles in turn (tile
+// t of wave w: tile 4t + w), so at any time they read one short run of each
+// plane; the rows of a token-level set are taken afterwards by the wave whose
+// consecutive tokens hold them.
+//
+// Every call splits its tokens over chunks and waves in this one way, whatever
+// its batch, its bound on the lengths or its workspace: a probability is rounded
+// to bf16 against the reference max that its wave has reached, so another split
+// would give other bits (2e-3 of an output's norm, for the same error against
+// exact arithmetic).
 //
 // One lane layout serves the K pass, the softmax and the V pass: NP = d/8
 // lanes per token row, each holding one 16-byte piece (8 channels), so one
@@ -49,8 +54,11 @@
 // wave index is scalar (the tile tests are uniform), a move of the reference max
 // crosses rows with permlane swaps, and the merge takes two channels a thread
 // from every copy instead of shuffling the copies together first.  Per layer
-// (split-K and merge, graph replay): 1001 tokens 18.3 -> 16.0 us with one
-// workgroup per chunk, 9.4 us with groups; 32768 tokens 31.3 -> 29.1 us.
+// (split-K and merge, graph replay): 1001 tokens 18.2 -> 15.6 us, 32768 tokens
+// 31.3 -> 29.1 us.  (A call of few chunks is bound by the chain of a wave's
+// sixteen tiles, some 0.7 us each: a workgroup per wave, which keeps the bits,
+// takes 14.9 us at 1001 tokens and 18.7 against 17.0 at 12288, whatever the
+// tiles in flight.)
 #pragma once
 
 #include "decode_shape.h"
@@ -229,7 +237,7 @@ __device__ __forceinline__ void row_gather(uint32_t x, uint32_t (&y)[G], int lan
   if constexpr (G >= 8) gather_stage<SH + 2, 4>(y, lane);
 }
 
-template <int D, int G, int SHAPE>
+template <int D, int G>
 struct SS {
   static constexpr int NP = D / 8;                 // lanes per row, one 16-byte piece each
   static constexpr int RPL = 64 / NP;              // rows per load instruction
@@ -239,18 +247,14 @@ struct SS {
   // (two rows per lane there too)
   static constexpr int TILE = D == 128 ? 8 : 16;
   static constexpr int NL = TILE / RPL;            // rows of a tile per lane
-  static constexpr int GW = kDecodeWaves;          // waves of a group, which take its tiles in turn
-  static constexpr int NGRP = SHAPE == kFull ? 1 : decode_groups(G);
-  static constexpr int GT = kDecodeWgTokens / NGRP;  // tokens of a group
-  static constexpr int W = SHAPE == kWide ? GW * NGRP : GW;  // waves of the workgroup
-  static constexpr int CW = GT / GW;               // tokens per wave
+  static constexpr int W = kDecodeWaves;           // waves of the workgroup, which take its tiles in turn
+  static constexpr int CW = kDecodeChunk;          // tokens per wave
   static constexpr int NT = CW / TILE;             // tiles per wave
   static constexpr int RS = D + 4;
   // tiles in flight behind the current one: dense heads, and residual heads
-  // with one entry per lane.  kSpread has few workgroups to a CU and registers
-  // to spare: every tile of a wave (up to four) is requested at the start.
-  static constexpr int PD0 = SHAPE == kSpread ? (NT < 4 ? NT - 1 : 3) : (NT < 3 ? NT - 1 : 2);
-  static constexpr int PD1 = SHAPE == kSpread ? PD0 : 1;
+  // with one entry per lane
+  static constexpr int PD0 = 2;
+  static constexpr int PD1 = 1;
   // accumulators of the workgroup's merge (floats), one copy per row of a
   // load of each wave; residual heads add their V entries to them
   static constexpr int SP = W * RPL * G * D;
@@ -284,10 +288,10 @@ __device__ __forceinline__ uint32_t residual_bytes(uint32_t m) {
 // MULTI: the call has several parts (spans and the exact tail); otherwise
 // part 0 is the only one, a compile-time constant, so the per-unit scalars
 // load straight from fixed argument offsets with no lookup in front.
-template <int D, int G, bool C8K, bool MULTI, int SHAPE>
-__global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kernel(DecodeParams P) {
-  using S = SS<D, G, SHAPE>;
-  constexpr int NTH = 64 * S::W, GW = S::GW, NGRP = S::NGRP;
+template <int D, int G, bool C8K, bool MULTI>
+__global__ __launch_bounds__((64 * SS<D, G>::W)) void decode_stream_kernel(DecodeParams P) {
+  using S = SS<D, G>;
+  constexpr int NTH = 64 * S::W;
   constexpr int NP = S::NP, RPL = S::RPL, TILE = S::TILE, NL = S::NL, CW = S::CW, W = S::W;
   constexpr uint32_t RB = D * 2;
   __shared__ float q_lds[D * G];                        // [c][g] fp32: residual K gathers
@@ -309,15 +313,11 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
   asm volatile("" : "+s"(scale_log2), "+s"(w1), "+s"(w2), "+s"(w3));
   DecodePart pt = P.part[0];
   if constexpr (!MULTI) asm volatile("" : "+s"(pt.lens), "+s"(pt.cache), "+s"(pt.modes), "+s"(pt.seg_off));
-  constexpr int NSUB = SHAPE == kSpread ? NGRP : 1;  // records per chunk
-  const uint32_t bx = blockIdx.x / NSUB;
+  const uint32_t bx = blockIdx.x;
   const uint32_t pair = by_chunks.div(bx);           // (sequence, rank of the KV head)
   const int slot = (int)(bx - pair * n_slots);
   const int seq = (int)by_hkv.div(pair);
   const int rank = (int)pair - seq * hkv;
-  // the wave's group, and its place in it
-  const int grp = SHAPE == kSpread ? (int)(blockIdx.x % NSUB) : wave / GW;
-  const int gwave = wave % GW;
   const int part = MULTI ? decode_part(P, slot) : 0;
   if constexpr (MULTI) pt = P.part[part];
   const int wgc = MULTI ? slot - P.part_base[part] : slot;
@@ -338,12 +338,12 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
     const uint64_t u0 = ((uint64_t)seq * n_blocks + block) * hkv;
     const auto* mw = as_const(reinterpret_cast<const uint32_t*>(pt.modes));
     const auto* so = as_const(pt.seg_off) + u0;
-    if (SHAPE == kFull && hkv <= 8) {
+    if (hkv <= 8) {
       // Workgroups are dispatched in index order, and the older of the waves
-      // sharing a SIMD are served first, so where they fill the chip the heads
-      // of a sequence are taken in cost order: residual heads (the most bytes
-      // per token) first, then the others, each group in head order.  (More
-      // than 8 KV heads keep the head order.)  Heads past the last repeat the
+      // sharing a SIMD are served first, so the heads of a sequence are taken
+      // in cost order: residual heads (the most bytes per token) first, then
+      // the others, each group in head order.  (More than 8 KV heads keep the
+      // head order.)  Heads past the last repeat the
       // last one's loads, which keeps the loads free of branches.
       const int hl = hkv - 1;
       const uint64_t w0 = u0 >> 2, w1 = (u0 + hl) >> 2;
@@ -376,11 +376,10 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
   const int sh = seq * hkv + head;   // the (sequence, KV head) of the record slots
   const uint32_t mbyte = mode_word & 0xFFu;
   const int mode = mode_of(mbyte);
-  const int grp_tok0 = wgc * kDecodeWgTokens + grp * S::GT;
-  const int wg_tok0 = SHAPE == kSpread ? grp_tok0 : wgc * kDecodeWgTokens;
-  float* rec = ws + (((uint64_t)sh * n_slots + slot) * NSUB + (SHAPE == kSpread ? grp : 0)) * G * S::RS;
+  const int tok0 = wgc * kDecodeWgTokens;  // the chunk's first token
+  float* rec = ws + ((uint64_t)sh * n_slots + slot) * G * S::RS;
   const bool bad_unit = !unit_byte_ok(mbyte, P.tokres ? P.n_rates : 0) || (seg_off & 255) != 0;
-  if (wg_tok0 >= T || bad_unit) {
+  if (tok0 >= T || bad_unit) {
     // no tokens here: an empty record, m = -inf, l = 0, acc = 0, since the
     // merge reads every slot; an invalid unit: m = 0, l = 1, acc = NaN, which
     // the merge carries into every output channel of the KV head's queries
@@ -432,7 +431,7 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
   }
 
   // the wave's CW consecutive tokens of a token-level set
-  const int wtok0 = grp_tok0 + gwave * CW;
+  const int wtok0 = tok0 + wave * CW;
 
   float m[G], l[G], acc[G][8];
   // scattered softmax state: the reference max of the lane's head and the
@@ -505,10 +504,8 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
     // the wave's tile t: rows from row0(t), nt of them in the sequence
     // (interleaved over the waves: 1.1% off the 8B decode step against a
     // contiguous 128 tokens a wave)
-    auto row0 = [&](int t) -> int { return grp_tok0 + (t * GW + gwave) * TILE; };
-    const int nt = grp_tok0 + gwave * TILE < T
-                       ? min(CW / TILE, (T - grp_tok0 - gwave * TILE + GW * TILE - 1) / (GW * TILE))
-                       : 0;
+    auto row0 = [&](int t) -> int { return tok0 + (t * W + wave) * TILE; };
+    const int nt = tok0 + wave * TILE < T ? min(CW / TILE, (T - tok0 - wave * TILE + W * TILE - 1) / (W * TILE)) : 0;
 
     // FP8 planes: a tile is one 1 KB block, and the lane's 16-byte slot of it
     // holds its piece of both of its rows (rows rg and rg + RPL)
@@ -827,26 +824,15 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
       // time: the lanes of row group rg rebuild the rg-th one in full,
       // K~ = M + sum_f w_f H_f and V~ alike, and fold it into the online
       // softmax.  The first one's row in the set: the running count before the
-      // 128-token chunk, plus the mask bits of the chunk's words before the
-      // wave's own.
+      // wave's tokens.
       constexpr int NF = Q4 ? 3 : 1;
-      static_assert(CW % 32 == 0 && kTokChunk % CW == 0, "whole mask words per wave, in one chunk");
+      static_assert(CW == kTokChunk, "a running count per wave");
       const uint32_t tw = (uint32_t)wtok0 >> 5;
-      const bool in_a = wtok0 + (lane & 32) < T && (lane & 32) < CW, in_b = wtok0 + 64 + (lane & 32) < T && 64 + (lane & 32) < CW;
+      const bool in_a = wtok0 + (lane & 32) < T, in_b = wtok0 + 64 + (lane & 32) < T;
       const uint32_t wa = __builtin_amdgcn_raw_buffer_load_b32(tmr, in_a ? (tw + (lane >> 5)) * 4 : kOob, 0, 0);
       const uint32_t wb = __builtin_amdgcn_raw_buffer_load_b32(tmr, in_b ? (tw + 2 + (lane >> 5)) * 4 : kOob, 0, 0);
-      uint32_t base = __builtin_amdgcn_raw_buffer_load_b32(
+      const uint32_t base = __builtin_amdgcn_raw_buffer_load_b32(
           tcr, wtok0 < T ? ((uint32_t)wtok0 / kTokChunk) * 4 : kOob, 0, 0);
-      if constexpr (CW < kTokChunk) {
-        constexpr int WPC = kTokChunk / 32;  // words of a chunk
-        uint32_t before[WPC - 1];
-#pragma unroll
-        for (int j = 0; j < WPC - 1; ++j)
-          before[j] = __builtin_amdgcn_raw_buffer_load_b32(
-              tmr, wtok0 < T && (uint32_t)j < tw % WPC ? (tw / WPC * WPC + j) * 4 : kOob, 0, 0);
-#pragma unroll
-        for (int j = 0; j < WPC - 1; ++j) base += (uint32_t)__builtin_popcount(before[j]);
-      }
       const bool bit_a = (wa >> (lane & 31)) & 1u, bit_b = (wb >> (lane & 31)) & 1u;
       const uint64_t ba = __ballot(bit_a), bb = __ballot(bit_b);
       const int na = __builtin_popcountll(ba), nres = na + __builtin_popcountll(bb);
@@ -1010,34 +996,24 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
     }
   }
   __syncthreads();
-  // Two channels a thread: a group's waves, then the workgroup's groups (the
-  // copies of a wave first).  The thread of channels 0 and 1 takes m and l too.
+  // Two channels a thread: the copies of a wave, then the workgroup's waves.
+  // The thread of channels 0 and 1 takes m and l too.
   for (int i = threadIdx.x; i < G * (D / 2); i += NTH) {
     const int g = i / (D / 2), c = 2 * (i % (D / 2));
-    float M = -INFINITY, gm[W / GW], f[W];
+    float M = -INFINITY, f[W];
 #pragma unroll
-    for (int u = 0; u < W / GW; ++u) {
-      gm[u] = -INFINITY;
+    for (int w = 0; w < W; ++w) M = fmaxf(M, m_lds[g][w]);
 #pragma unroll
-      for (int w = 0; w < GW; ++w) gm[u] = fmaxf(gm[u], m_lds[g][u * GW + w]);
-#pragma unroll
-      for (int w = 0; w < GW; ++w) f[u * GW + w] = merge_weight(m_lds[g][u * GW + w], gm[u]);
-      M = fmaxf(M, gm[u]);
-    }
+    for (int w = 0; w < W; ++w) f[w] = merge_weight(m_lds[g][w], M);
     // sum over the waves of x(wave, copy)
     auto total = [&](auto x) {
       float o = 0.f;
 #pragma unroll
-      for (int u = 0; u < W / GW; ++u) {
-        float go = 0.f;
+      for (int w = 0; w < W; ++w) {
+        float y = 0.f;
 #pragma unroll
-        for (int w = u * GW; w < u * GW + GW; ++w) {
-          float y = 0.f;
-#pragma unroll
-          for (int cp = 0; cp < RPL; ++cp) y += x(w, cp);
-          go = fmaf(f[w], y, go);
-        }
-        o = W == GW ? go : fmaf(merge_weight(gm[u], M), go, o);
+        for (int cp = 0; cp < RPL; ++cp) y += x(w, cp);
+        o = fmaf(f[w], y, o);
       }
       return o;
     };
@@ -1055,39 +1031,35 @@ __global__ __launch_bounds__((64 * SS<D, G, SHAPE>::W)) void decode_stream_kerne
   }
 }
 
-template <int D, int G, int SHAPE>
-static hipError_t launch_stream_shape(const DecodeParams& P, hipStream_t s) {
-  using S = SS<D, G, SHAPE>;
-  const dim3 grid((unsigned)P.batch * P.hkv * P.n_chunks_total * (SHAPE == kSpread ? S::NGRP : 1)), block(64 * S::W);
-  const bool multi = P.n_parts > 1 || P.tail_part >= 0;
-  if constexpr (SHAPE == kWide) {
-    if (multi) return hipErrorInvalidValue;  // several parts spread or take the full shape
-  } else if (multi) {
+template <int D, int G>
+static hipError_t launch_stream_g(const DecodeParams& P, hipStream_t s) {
+  const dim3 grid((unsigned)P.batch * P.hkv * P.n_chunks_total), block(64 * SS<D, G>::W);
+  if (P.n_parts > 1 || P.tail_part >= 0) {
     if (P.coef8)
-      hipLaunchKernelGGL((decode_stream_kernel<D, G, true, true, SHAPE>), grid, block, 0, s, P);
+      hipLaunchKernelGGL((decode_stream_kernel<D, G, true, true>), grid, block, 0, s, P);
     else
-      hipLaunchKernelGGL((decode_stream_kernel<D, G, false, true, SHAPE>), grid, block, 0, s, P);
+      hipLaunchKernelGGL((decode_stream_kernel<D, G, false, true>), grid, block, 0, s, P);
     return hipGetLastError();
   }
   if (P.coef8)
-    hipLaunchKernelGGL((decode_stream_kernel<D, G, true, false, SHAPE>), grid, block, 0, s, P);
+    hipLaunchKernelGGL((decode_stream_kernel<D, G, true, false>), grid, block, 0, s, P);
   else
-    hipLaunchKernelGGL((decode_stream_kernel<D, G, false, false, SHAPE>), grid, block, 0, s, P);
+    hipLaunchKernelGGL((decode_stream_kernel<D, G, false, false>), grid, block, 0, s, P);
   return hipGetLastError();
 }
 
-// The launches of one head dimension and shape, each compiled in a file of its own.
-template <int D, int SHAPE>
+// The launches of one head dimension, each compiled in a file of its own.
+template <int D>
 hipError_t launch_stream(const DecodeParams& P, hipStream_t s);
 
 #ifdef FDKV_STREAM_INSTANCES
-template <int D, int SHAPE>
+template <int D>
 hipError_t launch_stream(const DecodeParams& P, hipStream_t s) {
   switch (P.hq / P.hkv) {
-    case 1: return launch_stream_shape<D, 1, SHAPE>(P, s);
-    case 2: return launch_stream_shape<D, 2, SHAPE>(P, s);
-    case 4: return launch_stream_shape<D, 4, SHAPE>(P, s);
-    default: return launch_stream_shape<D, 8, SHAPE>(P, s);
+    case 1: return launch_stream_g<D, 1>(P, s);
+    case 2: return launch_stream_g<D, 2>(P, s);
+    case 4: return launch_stream_g<D, 4>(P, s);
+    default: return launch_stream_g<D, 8>(P, s);
   }
 }
 #endif

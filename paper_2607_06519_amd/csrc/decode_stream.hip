@@ -1,6 +1,5 @@
-// Streaming split-K decode over a bf16 or FP8 cache: the choice of launch
-// shape, and the merge of the records (all cache types).  The split-K kernel
-// is in decode_stream.h.
+// Streaming split-K decode over a bf16 or FP8 cache: its launch, and the merge
+// of the records (all cache types).  The split-K kernel is in decode_stream.h.
 #include "decode_stream.h"
 
 namespace fdkv {
@@ -41,11 +40,11 @@ __device__ __forceinline__ float wave_sum_dpp(float x) {
 // weights each chunk with the value read from the lane that owns it.  A
 // running (M, l, o) carries over between blocks; LDS adds the four waves'
 // partial sums.
-// SUB: records per chunk.  Above one (the split-K pass wrote a record per
-// group of a chunk's waves) each chunk's records are first folded into one, with the
-// arithmetic of a workgroup that holds all of the chunk's groups; chunks are
-// then taken four a wave at a time and those past the end skipped, as such
-// launches have few.
+// SUB: records per chunk.  Above one (the split-K pass of a small fp32 call wrote
+// a record per group of a chunk's waves) each chunk's records are first folded
+// into one, with the arithmetic of a workgroup that holds all of the chunk's
+// groups; chunks are then taken four a wave at a time and those past the end
+// skipped, as such launches have few.
 template <int D, bool BF16, int G, int SUB>
 __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams P) {
   constexpr int RS = D + 4;
@@ -142,24 +141,21 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams P) {
   }
 }
 
-// The launch shapes: decode_shape.h; their rule: kDecodeSmallChunks.
 hipError_t launch_decode_stream(const DecodeParams& P, hipStream_t s) {
   if (P.n_chunks_total <= 0) return hipSuccess;
-  if (P.d == 128) {
-    if (P.n_sub > 1) return launch_stream<128, kSpread>(P, s);
-    return P.wide ? launch_stream<128, kWide>(P, s) : launch_stream<128, kFull>(P, s);
-  }
-  if (P.n_sub > 1) return launch_stream<64, kSpread>(P, s);
-  return P.wide ? launch_stream<64, kWide>(P, s) : launch_stream<64, kFull>(P, s);
+  return P.d == 128 ? launch_stream<128>(P, s) : launch_stream<64>(P, s);
 }
 
 template <int D, bool BF16, int G>
 static hipError_t launch_merge_g(const DecodeParams& P, hipStream_t s) {
   const dim3 grid((unsigned)P.batch * P.hq);
-  if (P.n_sub > 1)
-    hipLaunchKernelGGL((decode_merge_kernel<D, BF16, G, decode_groups(G)>), grid, dim3(256), 0, s, P);
-  else
-    hipLaunchKernelGGL((decode_merge_kernel<D, BF16, G, 1>), grid, dim3(256), 0, s, P);
+  if constexpr (!BF16) {
+    if (P.n_sub > 1) {
+      hipLaunchKernelGGL((decode_merge_kernel<D, BF16, G, decode_groups(G)>), grid, dim3(256), 0, s, P);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((decode_merge_kernel<D, BF16, G, 1>), grid, dim3(256), 0, s, P);
   return hipGetLastError();
 }
 

@@ -192,6 +192,9 @@ void probe_split(ProbeParams* p, int units, int T, int bsize, int row_bytes, int
   }
 }
 
+// Bytes of a chunk's split-K record: (acc, m, l) of each query head of the KV head's group.
+uint64_t record_bytes(const fdkv_dims* d) { return (uint64_t)(d->n_q_heads / d->n_kv_heads) * (d->head_dim + 4) * 4; }
+
 uint64_t decode_chunks(int max_T) { return (uint64_t)(max_T + kDecodeWgTokens - 1) / kDecodeWgTokens; }
 
 // The split-K records of fdkv_decode_attn_static live in this file-scope
@@ -579,8 +582,10 @@ fdkv_status fdkv_decode_spans_workspace(const fdkv_dims* dims, int32_t batch, in
     n += decode_chunks(max_seq_lens[i]);
   }
   if (tail_cap >= 0) n += decode_chunks(tail_cap);
-  const uint64_t G = dims->n_q_heads / dims->n_kv_heads;
-  *bytes = (size_t)((uint64_t)batch * dims->n_kv_heads * std::max<uint64_t>(n, 1) * G * (dims->head_dim + 4) * 4);
+  uint64_t chunks = (uint64_t)batch * dims->n_kv_heads * std::max<uint64_t>(n, 1);
+  if (dims->dtype == FDKV_F32)  // room for a small call's record per group of a chunk's waves
+    chunks = std::max(chunks, decode_groups(dims->n_q_heads / dims->n_kv_heads) * std::min<uint64_t>(chunks, kDecodeSmallChunks));
+  *bytes = (size_t)(chunks * record_bytes(dims));
   return FDKV_OK;
 }
 
@@ -644,7 +649,6 @@ fdkv_status decode_impl(const fdkv_dims* dims, int32_t batch, int32_t n_spans, c
   if (!aligned(q, 16) || ((phases & kPhaseMerge) && !aligned(out, 16)) || !aligned(ws, 16) || !isfinite(sm_scale))
     return FDKV_E_INVALID_ARG;
   const uint64_t row = (uint64_t)dims->head_dim * elem_bytes(dims);
-  int32_t maxes[kMaxParts];
   for (int i = 0; i < n_spans; ++i) {
     const fdkv_span& sp = spans[i];
     if (sp.max_seq_len < 0 || !aligned(sp.seq_lens, 4) || !aligned(sp.modes, 4) || !aligned(sp.seg_offsets, 8) ||
@@ -654,16 +658,16 @@ fdkv_status decode_impl(const fdkv_dims* dims, int32_t batch, int32_t n_spans, c
     // the rows of a token-level residual set are addressed with 32-bit offsets too
     if (tokens_mode(dims) && residual_token_count((uint64_t)sp.max_seq_len, max_ppm(dims)) * 3 * row >= (1ull << 31))
       return FDKV_E_UNSUPPORTED;
-    maxes[i] = sp.max_seq_len;
   }
   if (tail) {
     if (tail->cap < 0 || !aligned(tail->lens, 4) || !aligned(tail->k, 16) || !aligned(tail->v, 16))
       return FDKV_E_INVALID_ARG;
     if ((uint64_t)tail->cap * row >= (1ull << 31)) return FDKV_E_UNSUPPORTED;
   }
-  size_t need = 0;
-  st = fdkv_decode_spans_workspace(dims, batch, n_spans, maxes, tail ? tail->cap : -1, &need);
-  if (st != FDKV_OK) return st;
+  // what the call cannot do without: one record per chunk
+  uint64_t slots = tail ? decode_chunks(tail->cap) : 0;
+  for (int i = 0; i < n_spans; ++i) slots += decode_chunks(spans[i].max_seq_len);
+  const uint64_t need = (uint64_t)batch * dims->n_kv_heads * std::max<uint64_t>(slots, 1) * record_bytes(dims);
   if (ws_bytes < need) return FDKV_E_WORKSPACE;
 
   DecodeParams p{};
@@ -709,11 +713,11 @@ fdkv_status decode_impl(const fdkv_dims* dims, int32_t batch, int32_t n_spans, c
   p.n_parts = n_parts;
   p.n_chunks_total = total;
   p.tail_part = tail ? n_spans : -1;
-  // A small call (decode_shape.h) spreads its chunks where it merges the
+  // A small fp32 call (kDecodeSmallChunks) spreads its chunks where it merges the
   // records itself and the workspace holds one per group; otherwise a one-part
   // call keeps a chunk's groups in one workgroup, which gives the same bits, so
   // that the two-phase calls and every workspace size agree with the one call.
-  const bool small = (int64_t)batch * dims->n_kv_heads * total <= kDecodeSmallChunks;
+  const bool small = !p.bf16 && (int64_t)batch * dims->n_kv_heads * total <= kDecodeSmallChunks;
   const int groups = decode_groups(p.hq / p.hkv);
   p.n_sub = small && phases == (kPhaseSplit | kPhaseMerge) && ws_bytes / groups >= need ? groups : 1;
   p.wide = small && p.n_sub == 1 && n_parts == 1 && !tail;
@@ -760,8 +764,7 @@ fdkv_status fdkv_decode_combine(const fdkv_dims* dims, int32_t batch, int32_t n_
   fdkv_status st = check_dims(dims);
   if (st != FDKV_OK) return st;
   if (batch < 1 || n_chunks < 1 || !aligned(out, 16) || !aligned(ws, 16)) return FDKV_E_INVALID_ARG;
-  const uint64_t G = dims->n_q_heads / dims->n_kv_heads;
-  const uint64_t need = (uint64_t)batch * dims->n_kv_heads * n_chunks * G * (dims->head_dim + 4) * 4;
+  const uint64_t need = (uint64_t)batch * dims->n_kv_heads * n_chunks * record_bytes(dims);
   if (ws_bytes < need) return FDKV_E_WORKSPACE;
   DecodeParams p{};
   p.out = out;

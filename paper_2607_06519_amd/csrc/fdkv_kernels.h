@@ -80,21 +80,19 @@ __host__ __device__ __forceinline__ int unit_ppm(int res_ppm, int n_rates, const
 constexpr int kDecodeChunk = 128;
 constexpr int kDecodeWaves = 4;
 constexpr int kDecodeWgTokens = kDecodeChunk * kDecodeWaves;
-// Groups of four waves that share a chunk of a small call (decode_shape.h):
+// Groups of four waves that share a chunk of a small fp32 call (decode_shape.h):
 // 128 tokens a group, or 256 with eight query heads, where the accumulators of
 // sixteen waves would pass the LDS of a workgroup.
 __host__ __device__ constexpr int decode_groups(int G) { return G == 8 ? 2 : 4; }
-// A decode call of at most this many chunks over all (sequence, KV head) pairs
-// is small: its chunks are split over groups of waves.  One
+// An fp32 decode call of at most this many chunks over all (sequence, KV head)
+// pairs is small: its chunks are split over groups of waves (kSpread, or kWide
+// where the workspace holds one record per chunk or the caller merges).  One
 // workgroup per chunk then leaves at least a quarter of the 256 CUs idle, and
-// each of the others is bound by what one CU can keep in flight (a chunk of
-// 512 tokens is 262 KB).  Per layer on the 8B shape (8 KV heads, one sequence),
-// one workgroup per chunk against groups: 16 chunks 16.0 and 9.4 us, 64 chunks
-// 16.2 and 11.0, 128 chunks 17.8 and 14.0, 200 chunks 18.1 and 17.8, 256 chunks
-// 19.5 and 20.4, 512 chunks 29.1 and 32.6 (more groups than the CUs run at once,
-// and four times the records to merge).  Eight query heads: 128 chunks 24.1 and
-// 18.8 us, 256 chunks 24.6 and 25.9; head dimension 64: 128 chunks 11.5 and
-// 10.2, 256 chunks 12.8 and 14.1.
+// each of the others is bound by what one CU can keep in flight.  Per layer on
+// the 8B shape (8 KV heads, one sequence; kFull, kWide and kSpread): 16 chunks
+// 71.6, 64.2 and 23.9 us, 128 chunks 83.9, 75.7 and 37.5, 192 chunks 85.3, 79.6
+// and 48.1.  Eight query heads to a KV head, 192 chunks: 145, 122 and 95 us;
+// head dimension 64: 47.0, 41.2 and 31.1.
 constexpr int kDecodeSmallChunks = 192;
 constexpr int kMaxParts = 16;       // compressed spans plus the exact tail of one decode call
 

@@ -247,6 +247,21 @@ def test_generation_entry_points_validate(lib):
                            None) == -1
 
 
+@pytest.mark.parametrize("hkv,hq,room", [(2, 8, 4), (2, 16, 2)])
+def test_decode_workspace_holds_a_record_per_group_for_small_fp32_calls(lib, hkv, hq, room):
+    """One record per chunk; for an fp32 cache of up to 192 chunks one per group of a chunk's waves, and
+    never less for a longer call, so that a workspace sized for the longest one serves them all."""
+    for dtype in ("f32", "bf16", "bf16_e4m3"):
+        dm = B.dims(4, hkv, hq, 128, 16, dtype)
+        rec, last = hq // hkv * 132 * 4, 0
+        for T in (0, 1, 512, 513, 96 * 512, 96 * 512 + 1, 96 * 512 * room, 96 * 512 * room + 1):
+            chunks = hkv * max(-(-T // 512), 1)
+            want = max(chunks, room * min(chunks, 192)) if dtype == "f32" else chunks
+            got = B.decode_workspace(dm, 1, T)
+            assert got == want * rec and got >= last, (dtype, T)
+            last = got
+
+
 # ---------------------------------------------------------------- token-level residual set
 @pytest.mark.parametrize("dtype,d,ppm,sched", [("bf16", 128, 50000, B.PAIRS), ("f32", 64, 123456, B.QUADS),
                                                ("bf16_e4m3", 128, 1000000, B.MIXED), ("bf16", 64, 0, B.MIXED)])
