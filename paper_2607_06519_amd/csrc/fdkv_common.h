@@ -177,19 +177,14 @@ FDKV_HD uint32_t pack_bf16x2(float lo, float hi) {
 // Gram matrix of x taken as H H^T + H L^T + L H^T carries only that error
 // (plus the dropped L L^T, 2^-18 relative), where H H^T alone would carry
 // the bf16 rounding of x (2^-9 relative per element).
-// The differences x - hi come from bf16 dot products of the pair hi with
-// (-1, 0) and (0, -1) on top of x (exact, like the subtraction of the widened
-// value, which is one instruction more).
+// Each low half depends on its own value alone: an infinite x (or one that
+// rounds to an infinite hi) makes its own low half NaN, not its neighbour's.
+// (Two bf16 dot products of the pair hi with (-1, 0) and (0, -1) are two
+// instructions fewer than the subtractions of the widened values, but multiply
+// the neighbour by 0, which is NaN for an infinite one.)
 __device__ __forceinline__ void split_bf16x2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
-  typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
   hi = cvt_bf16x2(x0, x1);
-  const bf16x2v h = __builtin_bit_cast(bf16x2v, hi);
-  // kept from the compiler as bit patterns: as the constant pair (-1, 0) the
-  // first became the inline constant -1.0, which the instruction reads as (0, -1)
-  uint32_t m0 = 0x0000BF80u, m1 = 0xBF800000u;
-  asm("" : "+s"(m0), "+s"(m1));
-  lo = cvt_bf16x2(__builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2v, m0), x0, false),
-                  __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2v, m1), x1, false));
+  lo = cvt_bf16x2(x0 - bf16_lo(hi), x1 - bf16_hi(hi));
 }
 #endif
 
