@@ -562,8 +562,10 @@ __global__ __launch_bounds__(512) void probe_dgram4_kernel(ProbeParams P) {
           // v = b Z_1 - a Z_3, w = Z_2 / 2 the layers' images are w + u,
           // v - w, -v - w, w - u, and the deviations (mean less layer) their
           // negatives.
+          // A layer that is not finite makes Z_2 so, and the reconstruction
+          // with it, whether Z_2 is kept or not: hence the product.
           const float k1 = (kept >> (3 * c)) & 1u ? 0.f : z1;
-          const float k2 = (kept >> (3 * c + 1)) & 1u ? 0.f : z2;
+          const float k2 = z2 * ((kept >> (3 * c + 1)) & 1u ? 0.f : 1.f);
           const float k3 = (kept >> (3 * c + 2)) & 1u ? 0.f : z3;
           const float u = fmaf(kDct4A, k1, kDct4B * k3), v = fmaf(kDct4B, k1, -(kDct4A * k3));
 #pragma unroll

@@ -31,3 +31,18 @@ def test_an_infinite_kept_channel_leaves_a_pairs_residual_loss_finite(dtype, d, 
         want /= 2 * G * P * d
         got = err[0, h].tolist()
         assert not math.isfinite(got[0]) and abs(got[1] - want) <= 2e-5 * want, (h, got, want)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+def test_an_infinite_layer_reaches_both_losses_of_a_block_of_four(dtype, d):
+    """The mean of the four layers and every coefficient are infinite there: so is what decode would rebuild."""
+    import torch
+    from paper_2607_06519_amd import binding as B
+    from paper_2607_06519_amd.cache import probe
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator("cuda").manual_seed(d)
+    kl = [torch.randn(2, 100, d, generator=g, device="cuda").to(tdt) for _ in range(4)]
+    q = [torch.randn(4, 24, d, generator=g, device="cuda").to(tdt) for _ in range(4)]
+    kl[2][1, 33, 5] = math.inf
+    err, _ = probe(B.dims(4, 2, 4, d, 8, dtype, B.QUADS), 100, kl, q, 24)
+    assert torch.isfinite(err[0, 0]).all() and not torch.isfinite(err[0, 1]).any()
