@@ -293,6 +293,7 @@ __global__ __launch_bounds__(score_threads(D), 2) void token_score_bf16_kernel(T
       const int layer = first + (NB == 2 ? ly : pass);
       const auto qr = make_rsrc(static_cast<const uint8_t*>(P.qp[layer]) + (uint64_t)head * qspan, qspan);
       const int rounds = (GP + R - 1) / R;
+      const int whole = (GP + 31) / R;  // rounds with rows in both blocks of 32: the last one may have none in the second
       uint4 next[PER];
       auto fetch = [&](int r) {  // rows past the last read zeros: logits of 0
 #pragma unroll
@@ -350,7 +351,7 @@ __global__ __launch_bounds__(score_threads(D), 2) void token_score_bf16_kernel(T
       for (int st = 0; st < 2; ++st)
 #pragma unroll
         for (int r = 0; r < 16; ++r) a1[st][r] = 0.f;  // of no rows yet
-      for (int r = 0; r < rounds; ++r) {
+      for (int r = 0; r < whole; ++r) {
         const uint16_t* tile = qs[r & 1];
         if (r + 1 < rounds) {
           stage((r + 1) & 1);
@@ -365,6 +366,12 @@ __global__ __launch_bounds__(score_threads(D), 2) void token_score_bf16_kernel(T
         __syncthreads();
       }
       take(a1);
+      // 32 zero rows are not multiplied with an infinite deviation (a row of the
+      // first block past the last one is, as in every tile)
+      if (whole < rounds) {
+        block(qs[whole & 1], a0);
+        take(a0);
+      }
     }
   }
   // lanes l and l + 32 saw the other 16 rows of each block for the same token

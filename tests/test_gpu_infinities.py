@@ -46,3 +46,21 @@ def test_an_infinite_layer_reaches_both_losses_of_a_block_of_four(dtype, d):
     kl[2][1, 33, 5] = math.inf
     err, _ = probe(B.dims(4, 2, 4, d, 8, dtype, B.QUADS), 100, kl, q, 24)
     assert torch.isfinite(err[0, 0]).all() and not torch.isfinite(err[0, 1]).any()
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("rows", [32, 64, 96])
+def test_an_infinite_deviation_makes_the_shared_loss_of_a_token_set_infinite(d, rows):
+    """bf16 probe rows in multiples of 32 are not padded with rows of zeros, whose product with an infinite
+    deviation is NaN: the token's score and the shared loss are infinite."""
+    import torch
+    from paper_2607_06519_amd import binding as B
+    from paper_2607_06519_amd.cache import probe
+    G, T = 2, 200
+    g = torch.Generator("cuda").manual_seed(d + rows)
+    kl = [torch.randn(1, T, d, generator=g, device="cuda").bfloat16() for _ in range(2)]
+    q = [torch.randn(G, rows // G, d, generator=g, device="cuda").bfloat16() for _ in range(2)]
+    kl[0][0, 57, 3] = math.inf
+    err, score = probe(B.dims(2, 1, G, d, 0, "bf16", B.PAIRS, B.RES_TOKENS, 50000), T, kl, q, rows // G)
+    assert score[0, 0, 57] == math.inf and err[0, 0, 0] == math.inf
+    assert int(torch.isfinite(score).sum()) == T - 1
