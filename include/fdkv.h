@@ -210,7 +210,12 @@ fdkv_status fdkv_selection_bytes(const fdkv_dims* dims, int32_t seq_len, size_t*
  *              routed fractions (E_residual at each)
  *   token_scores_out  FDKV_RES_TOKENS: device float [n_blocks][Hkv][T], out: s_t
  *                     (the residual loss then keeps the top ceil(r T) tokens); else unused
- *   ws         device workspace of >= fdkv_probe_workspace() bytes
+ *   ws         device workspace of fdkv_probe_workspace() bytes.  (A call needs L x Hkv x
+ *              d x d x 4 bytes, and 8 per 1024 tokens and unit, each rounded up to 256;
+ *              FDKV_RES_TOKENS: 4 per token and unit.  FDKV_E_WORKSPACE otherwise.)  The
+ *              losses are fp32 sums of at most 1024 tokens each, added in fp64; how many
+ *              tokens each takes depends on T, the number of units and the workspace,
+ *              and so do the last bits of a unit's loss.
  *   k_select_out  device, NULL or fdkv_selection_bytes() bytes (4-byte aligned), out:
  *              the per-token residual selection of K that the residual loss uses
  *              (Eq. 3), for fdkv_compress of the same keys to reuse; unused with

@@ -12,6 +12,7 @@
 #include "fdkv.h"
 #include "fdkv_common.h"
 #include "fdkv_kernels.h"
+#include "probe_split.h"
 
 using namespace fdkv;
 
@@ -144,52 +145,26 @@ Sched sched_of(const fdkv_dims* d) {
   return s;
 }
 
-uint64_t probe_chunks(int T) { return (uint64_t)(T + kProbeChunk - 1) / kProbeChunk; }
-
-// Probe workspace: probe Gram matrices per (layer, KV head) and per-chunk
-// partials (every block finds its top-k inside its Gram kernel).
+// Probe workspace: probe Gram matrices per (layer, KV head) and the
+// workgroups' partials (every block finds its top-k inside its Gram kernel).
+// `total` holds a partial per kProbeLeast tokens; `least`, one per kProbeMost,
+// is what a call accepts.
 struct ProbeWs {
-  uint64_t gram, part, total;
+  uint64_t gram, part, total, least;
 };
 ProbeWs probe_ws_layout(const fdkv_dims* d, int T) {
   const Sched sch = sched_of(d);
   const uint64_t units = (uint64_t)sch.n * d->n_kv_heads;
   ProbeWs w{};
   if (tokens_mode(d)) {  // the token scores' sums of squares
-    w.total = plane_bytes(units * (uint64_t)T * 4);
+    w.total = w.least = plane_bytes(units * (uint64_t)T * 4);
     return w;
   }
   w.gram = 0;
   w.part = w.gram + plane_bytes((uint64_t)d->n_layers * d->n_kv_heads * d->head_dim * d->head_dim * 4);
-  w.total = w.part + plane_bytes(units * probe_chunks(T) * 2 * 4);
+  w.total = w.part + plane_bytes(units * probe_partials(T, kProbeLeast) * 2 * 4);
+  w.least = w.part + plane_bytes(units * probe_partials(T, kProbeMost) * 2 * 4);
   return w;
-}
-
-// Workgroups per unit of a deviation Gram launch, and the tokens of each.  A
-// launch of `units` units of `steps` steps runs in rounds of as many
-// workgroups as the chip holds: `at_once`, 256 CUs times those that a CU holds
-// (two of pairs, by registers; one of blocks of four, by LDS).  Of the counts
-// that the workspace holds partials for, the one of the least cost is taken:
-// the steps over all rounds, a workgroup's start and its contraction with the
-// probe Gram matrix counted as a step, plus a quarter of a workgroup's steps,
-// as they don't end together.  Against 1024 tokens a workgroup on the 8B shape
-// in the default block setting at 12345 tokens (48 units of four: 624
-// workgroups, the third round nearly empty) the probe takes 638 in place of 705 us;
-// where the rounds come out even it stays within 2% (8B pairs, 32768 tokens:
-// 834 and 845 us).
-void probe_split(ProbeParams* p, int units, int T, int bsize, int row_bytes, int cap) {
-  const int rows = probe_rows(bsize, row_bytes), at_once = 256 * (bsize == 2 ? 2 : 1);
-  const int64_t steps = (T + rows - 1) / rows;
-  int64_t best = INT64_MAX;
-  for (int n = 1; n <= cap; ++n) {
-    const int64_t each = (steps + n - 1) / n, used = (steps + each - 1) / each;
-    const int64_t cost = 4 * ((units * used + at_once - 1) / at_once) * (each + 1) + each;
-    if (cost <= best) {
-      best = cost;
-      p->chunk_tokens = (int)(each * rows);
-      p->n_chunks = (int)used;
-    }
-  }
 }
 
 // Bytes of a chunk's split-K record: (acc, m, l) of each query head of the KV head's group.
@@ -428,7 +403,7 @@ fdkv_status fdkv_probe(const fdkv_dims* dims, int32_t seq_len, const void* const
   for (int l = 0; l < dims->n_layers; ++l)
     if (!aligned(k_layers[l], 16) || !aligned(qp_layers[l], 16)) return FDKV_E_INVALID_ARG;
   const ProbeWs w = probe_ws_layout(dims, seq_len);
-  if (ws_bytes < w.total) return FDKV_E_WORKSPACE;
+  if (ws_bytes < w.least) return FDKV_E_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint8_t* base = static_cast<uint8_t*>(ws);
 
@@ -482,14 +457,18 @@ fdkv_status fdkv_probe(const fdkv_dims* dims, int32_t seq_len, const void* const
   pp.d = dims->head_dim;
   pp.topk = dims->topk;
   pp.n_probe = n_probe;
-  pp.max_chunks = (int)probe_chunks(seq_len);
+  pp.max_chunks = (int)probe_partials(seq_len, ws_bytes >= w.total ? kProbeLeast : kProbeMost);
   pp.bf16 = dims->dtype != FDKV_F32;
   for (int B = 2; B <= 4; B += 2) {
     pp.bl = blocks_of_size(sch, B);
     pp.bsize = B;
     if (pp.bl.n == 0) continue;
-    probe_split(&pp, pp.bl.n * pp.hkv, seq_len, B, (int)row_bytes, pp.max_chunks);
-    pp.used_chunks[B == 4] = pp.n_chunks;
+    // workgroups that the chip holds: two to a CU of bf16 pairs; one of fp32
+    // pairs (registers) and of blocks of four (LDS)
+    const int at_once = 256 * (B == 2 && pp.bf16 ? 2 : 1);
+    const ProbeSplit sp = probe_split(pp.bl.n * pp.hkv, seq_len, probe_rows(B, (int)row_bytes), at_once, pp.max_chunks);
+    pp.chunk_tokens = sp.chunk_tokens;
+    pp.n_chunks = pp.used_chunks[B == 4] = sp.n_chunks;
     const hipError_t e = launch_probe(pp, s);  // every block takes its top-k inside its Gram kernel
     if (e != hipSuccess) return hip_fail(e, "probe");
   }

@@ -156,7 +156,6 @@ struct AppendParams {
 };
 
 // probe
-constexpr int kProbeChunk = 1024;   // the workspace holds a partial per this many tokens of a unit
 // tokens per step of the deviation Gram kernels
 __host__ __device__ constexpr int probe_rows(int bsize, int row_bytes) {
   return bsize == 2 || 512 / (row_bytes / 16) > 32 ? 64 : 32;
