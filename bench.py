@@ -23,11 +23,12 @@ default workload) the decode lines of the 16-sequence batch and the 70B-shaped
 from __future__ import annotations
 
 import argparse
+import glob
 import hashlib
-import re
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -135,15 +136,24 @@ def code_tokens(text):
 
 
 def kernel_source_hash(read=None):
-    """Hash of the code the decode kernels build from; counter runs recorded under another hash
-    are not used.  ``read(name)`` returns a file's text (default: the working tree)."""
+    """Hash of the code the decode kernels build from (the decode*.hip files and the headers of the
+    library that they include, directly or not); counter runs recorded under another hash are not
+    used.  ``read(name)`` returns a file's text (default: the working tree)."""
+    csrc = os.path.join(ROOT, "paper_2607_06519_amd", "csrc")
     if read is None:
         def read(name):
-            with open(os.path.join(ROOT, "paper_2607_06519_amd", "csrc", name)) as f:
+            with open(os.path.join(csrc, name)) as f:
                 return f.read()
+    todo, seen = sorted(os.path.basename(p) for p in glob.glob(os.path.join(csrc, "decode*.hip"))), set()
     h = hashlib.sha256()
-    for name in ("decode.hip", "decode_stream.hip", "decode_stream.h", "decode_shape.h", "fdkv_common.h", "fdkv_kernels.h"):
-        h.update(code_tokens(read(name)).encode())
+    while todo:
+        name = todo.pop(0)
+        if name in seen or not os.path.exists(os.path.join(csrc, name)):
+            continue
+        seen.add(name)
+        text = read(name)
+        h.update(code_tokens(text).encode())
+        todo += re.findall(r'#include "([^"]+)"', text)
     return h.hexdigest()[:16]
 
 

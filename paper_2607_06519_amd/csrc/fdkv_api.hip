@@ -692,11 +692,11 @@ fdkv_status decode_impl(const fdkv_dims* dims, int32_t batch, int32_t n_spans, c
   p.n_parts = n_parts;
   p.n_chunks_total = total;
   p.tail_part = tail ? n_spans : -1;
-  // A small fp32 call (kDecodeSmallChunks) spreads its chunks where it merges the
+  // A small fp32 call (decode_small) spreads its chunks where it merges the
   // records itself and the workspace holds one per group; otherwise a one-part
   // call keeps a chunk's groups in one workgroup, which gives the same bits, so
   // that the two-phase calls and every workspace size agree with the one call.
-  const bool small = !p.bf16 && (int64_t)batch * dims->n_kv_heads * total <= kDecodeSmallChunks;
+  const bool small = decode_small(p.bf16, (int64_t)batch * dims->n_kv_heads * total);
   const int groups = decode_groups(p.hq / p.hkv);
   p.n_sub = small && phases == (kPhaseSplit | kPhaseMerge) && ws_bytes / groups >= need ? groups : 1;
   p.wide = small && p.n_sub == 1 && n_parts == 1 && !tail;

@@ -94,6 +94,7 @@ __host__ __device__ constexpr int decode_groups(int G) { return G == 8 ? 2 : 4; 
 // and 48.1.  Eight query heads to a KV head, 192 chunks: 145, 122 and 95 us;
 // head dimension 64: 47.0, 41.2 and 31.1.
 constexpr int kDecodeSmallChunks = 192;
+__host__ __device__ constexpr bool decode_small(bool bf16, int64_t chunks) { return !bf16 && chunks <= kDecodeSmallChunks; }
 constexpr int kMaxParts = 16;       // compressed spans plus the exact tail of one decode call
 
 // One part of a decode call (a compressed span or the exact tail); its

@@ -1,10 +1,13 @@
 """Host-side logic of bench.py: the one-GPU refusal and the rocprofv3 summaries
 that the bench line's roofline figures come from (no GPU involved)."""
 import csv
+import importlib.util
 import json
 import os
 import subprocess
 import sys
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -60,3 +63,21 @@ def test_pmc_summary_scales_by_the_calibration_copy(tmp_path):
     assert rec["bytes_per_launch"] == (1000 * 2 + 5) * 1024
     assert rec["combine_bytes"] == 10 * 2 * 1024
     assert rec["kernels"] == ["decode_stream_kernel"]
+
+
+@pytest.mark.parametrize("name", ["decode_stream.h", "decode_stream_d64.hip", "decode_stream_d128.hip", "decode.hip",
+                                  "decode_shape.h", "divu.h", "fdkv_kernels.h", "fdkv_common.h"])
+def test_traffic_records_expire_with_every_source_of_the_decode(name):
+    """A recorded HBM traffic counts only for the code that it was measured on: a change of code in any
+    file that the decode kernels build from changes the hash, a change of comments does not."""
+    spec = importlib.util.spec_from_file_location("bench_module", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+
+    def read(added):
+        def text(n):
+            with open(os.path.join(ROOT, "paper_2607_06519_amd", "csrc", n)) as f:
+                return f.read() + (added if n == name else "")
+        return bench.kernel_source_hash(text)
+
+    assert read("// a comment\n") == bench.kernel_source_hash() != read("int changed;\n")
