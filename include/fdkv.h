@@ -372,7 +372,7 @@ typedef struct {
 fdkv_status fdkv_append(const fdkv_dims* dims, int32_t batch, const int32_t* pos, int32_t cap,
                         const void* k_new, const void* v_new, void* tail_k, void* tail_v, void* stream);
 
-/* Device workspace bytes fdkv_decode_spans needs: max_seq_lens host [n_spans],
+/* Device workspace bytes for fdkv_decode_spans: max_seq_lens host [n_spans],
  * tail_cap the tail's cap, or -1 for no tail.  At most 16 parts (spans + tail). */
 fdkv_status fdkv_decode_spans_workspace(const fdkv_dims* dims, int32_t batch, int32_t n_spans,
                                         const int32_t* max_seq_lens, int32_t tail_cap, size_t* bytes);

@@ -10,7 +10,8 @@ namespace fdkv {
 // Launch shapes of a chunk of 512 tokens (one split-K record) of an fp32 cache.
 //  kFull   - one workgroup of 4 waves, 128 tokens a wave.
 //  kWide   - one workgroup of 4 NGRP waves; a group of 4 waves takes
-//            512 / NGRP consecutive tokens.
+//            512 / NGRP consecutive tokens.  (d = 128: sixteen waves hold it to
+//            128 VGPRs, 12 spilled at two query heads and 23 at four.)
 //  kSpread - the groups of kWide as NGRP workgroups, each writing a record of
 //            its own, which the merge folds into the chunk's record with
 //            kWide's arithmetic (the two give the same bits).

@@ -45,18 +45,17 @@
 // The waves merge in LDS and write one (acc, m, l) record per workgroup;
 // decode_merge combines the records.  HBM bound: no MFMA.
 //
-// What a small call spends outside the walk counts as much as the walk
-// (s_memrealtime stamps at 1001 tokens, 8B shape, before / now): unit scalars
-// known 1.3 us after the start, first tiles requested at 2.3 us, walk 1.7 us,
-// merge and record 1.9 us.  So the launch constants are read in one go and kept
-// in scalar registers, indices are divided by multiplication (divu.h), plane
-// sizes are 32-bit, each residual flavour computes only its own planes, the
-// wave index is scalar (the tile tests are uniform), a move of the reference max
-// crosses rows with permlane swaps, and the merge takes two channels a thread
-// from every copy instead of shuffling the copies together first.  Per layer
-// (split-K and merge, graph replay): 1001 tokens 18.2 -> 15.6 us, 32768 tokens
-// 31.3 -> 29.1 us.  (A call of few chunks is bound by the chain of a wave's
-// sixteen tiles, some 0.7 us each: a workgroup per wave, which keeps the bits,
+// What a workgroup spends outside its walk counts too (s_memrealtime stamps at
+// 1001 tokens, 8B shape, before the following: unit scalars known 1.3 us after
+// the start, first tiles requested at 2.3 us, merge and record 1.9 us).  So the
+// launch constants are read in one go and kept in scalar registers, indices are
+// divided by multiplication (divu.h), plane sizes are 32-bit, each residual
+// flavour computes only its own planes, the wave index is scalar (the tile tests
+// are uniform), a move of the reference max crosses rows with permlane swaps, and
+// the merge takes two channels a thread from every copy instead of shuffling the
+// copies together first.  Per layer (split-K and merge, graph replay): 1001
+// tokens 18.2 -> 15.6 us, 32768 tokens 31.3 -> 29.1 us.  (A call of few chunks is bound by the chain of a wave's
+// sixteen tiles, some 0.6 us each: a workgroup per wave, which keeps the bits,
 // takes 14.9 us at 1001 tokens and 18.7 against 17.0 at 12288, whatever the
 // tiles in flight.)
 #pragma once

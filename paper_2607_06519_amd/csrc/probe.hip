@@ -285,10 +285,11 @@ __global__ __launch_bounds__(256) void probe_qgram_mfma_kernel(ProbeParams P) {
 // blocks of D D^T ~ H H^T + H L^T + L H^T, waves 4-7 those of Dbar.  Eight
 // waves keep the accumulators at three blocks a wave, so four waves fit on a
 // SIMD for the VALU-heavy selection.  The next step's loads are in flight
-// during the MFMAs.  VALU bound (about 580 instructions a wave and step, three
+// during the MFMAs.  VALU bound (about 600 instructions a wave and step, three
 // quarters of the issue slots); without the MFMA phase the 8B probe at 32768
-// tokens would take 575 us, without the selection 690, as it is 810 (862 with
-// padded LDS rows and the blocks dealt round-robin).
+// tokens would take 575 us, without the selection 690, with both 810 (862 with
+// padded LDS rows and the blocks dealt round-robin; measured with two
+// instructions less a pair of channels in split_bf16x2, 1% of the time).
 template <int D, bool BF16>
 __global__ __launch_bounds__(512, BF16 ? 4 : 2) void probe_dgram_kernel(ProbeParams P) {
   constexpr int E = BF16 ? 2 : 4;
@@ -468,7 +469,8 @@ __global__ __launch_bounds__(512, BF16 ? 4 : 2) void probe_dgram_kernel(ProbePar
 // them), the token's top-k among the row's 3d coefficients with the other
 // lanes of the row (row_topk_mask), the block mean, the layer deviations (of
 // the residual reconstruction: the images of the coefficients not kept), and
-// writes the eight deviation rows to LDS as bf16 hi + lo pairs (split_bf16x2); wave w
+// writes the eight deviation rows to LDS as bf16 hi + lo pairs (split_bf16x2; fp32
+// keys of 128 channels spill 11 VGPRs here, the other forms none); wave w
 // accumulates layer w / 2, shared (w even) or residual (w odd), as
 // H H^T + H L^T + L H^T.
 template <int D, bool BF16>

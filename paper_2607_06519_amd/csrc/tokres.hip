@@ -235,10 +235,12 @@ __global__ __launch_bounds__(kScoreThreads) void token_score_kernel(TokenParams 
 // every bank once.  At d = 128 four waves a workgroup, two workgroups to a CU:
 // one builds its deviations while the other multiplies (eight waves in one
 // workgroup took 5% longer, 25% with blocks of four).  Bound by MFMA and VALU
-// issue together (51% and 35% of the cycles at eight waves).  Probe of 16 layers
-// of the 8B shape against one 32-row tile with a barrier on each side: 32768
-// tokens 1042 -> 994 us (pairs), 2450 -> 1734 (blocks of four), 648 -> 543 at
-// d = 64; 500 tokens 92 -> 51.
+// issue together (64% and 47% of the cycles).  Blocks of four at d = 128 spill 109
+// VGPRs of the two accumulator pairs, the deviations and the next rows (432 bytes
+// of scratch a lane).  Probe of 16 layers of the 8B shape against one 32-row tile
+// with a barrier on each side: 32768 tokens 1042 -> 970 us (pairs), 2450 -> 1652
+// (blocks of four), 648 -> 518 at d = 64; 500 tokens 92 -> 46.  (fp32 rows and
+// keys keep that older form, token_score_kernel.)
 constexpr int score_threads(int d) { return d == 128 ? 256 : 512; }
 
 template <int D, int NB>
